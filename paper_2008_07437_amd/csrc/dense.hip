@@ -2,14 +2,12 @@
 // GEMM tasks; log|Sigma| = 2 sum log L_jj and Z^T Sigma^-1 Z = ||L^-1 Z||^2).
 //
 // Storage: lower tiles of nb x nb, column-major inside a tile (ld = nb).
-// Right-looking factorisation with a look-ahead of one tile column: the
-// panel of column k+1 (update of that column, then its factorisation) runs on
-// a second stream while the trailing update of step k runs on the caller's
-// stream.  The panel itself is factored in 128-wide inner blocks: a
-// single-workgroup LDS Cholesky + triangular inverse of the 128 x 128
-// diagonal block, then the rows below are solved as an in-place GEMM with
-// the inverse, and the rest of the panel gets a rank-128 update.  Every
-// GEMM-shaped step runs on v_mfma_f64_16x16x4_f64.
+// Right-looking factorisation with a look-ahead of one diagonal tile: tile
+// (k+1, k+1) is updated and factored on a second stream (in 64-wide steps,
+// chol.hip) while the trailing update of step k runs on the caller's stream;
+// the rest of a tile column is solved as a GEMM with the tile's inverse.  Once
+// the trailing matrix is small, all of it goes through the 64-wide steps.
+// Every GEMM-shaped step runs on v_mfma_f64_16x16x4_f64.
 #include <algorithm>
 #include <cstdlib>
 
@@ -281,13 +279,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #undef MVG_STB
 }
 
-// ------------------------------------------------------------ panel kernels
+// ------------------------------------------------------- look-ahead kernel
 //
-// The panel of tile column k (rows k nb .. Np, width nb) is factored in
-// 64-wide inner blocks.  Every panel kernel is small (<= 32 KB LDS, about 100
-// VGPRs per lane) so that it can be resident on a CU next to two
-// trailing-update workgroups: the look-ahead panel never waits for the
-// trailing GEMM to drain.
+// Small (32 KB LDS, about 100 VGPRs per lane), so that it can be resident on
+// a CU next to two trailing-update workgroups: the look-ahead never waits for
+// the trailing GEMM to drain.
 constexpr int PB = 64;
 constexpr int SMALL_LDS = 2 * 2 * PB * KB;  // doubles (32 KB)
 
@@ -661,11 +657,17 @@ int launch_syrk_next(const mvg_mat *A, int k, hipStream_t st) {
   return check_launch("syrk64");
 }
 
-// Factor the diagonal tile (k, k) in place and fill W_k = L_kk^-1: 64-wide
+// Factor the diagonal tile (k, k) of a mixed-precision matrix in place and
+// fill W_k = L_kk^-1 (other matrices: diag_factor, 3-4 times faster).  The
+// mixed path rounds its panels to 16 or 24 bits, so any other order of the
+// FP64 operations here flips some of those roundings: with diag_factor
+// log|Sigma| at n = 25,600 moved by 4e-10 relative (Eq. (1) by 2e-8, as its
+// terms cancel), far above the 1e-13 of the FP64 path, for 8 % of the time.
+// 64-wide
 // inner blocks (register Cholesky + inverse of the block, in-tile TRSM and
 // update), then the off-diagonal blocks of W_k by block distance.
-int diag_factor(const TileMap &M, int k, double *winv, int64_t *d_info, const PivotTol &pt,
-                hipStream_t st) {
+int diag_factor_mixed(const TileMap &M, int k, double *winv, int64_t *d_info, const PivotTol &pt,
+                      hipStream_t st) {
   const int s = M.nb / PB;
   hipLaunchKernelGGL(k_zero_upper_blocks, dim3(64), dim3(256), 0, st, M.nb, k, winv);
   if (int rc = check_launch("zero_upper_blocks")) return rc;
@@ -810,6 +812,14 @@ static int panel_trsm(const TileMap &M, int k, const double *winv, double *P, hi
   return launch_trail<TRAIL_TRSM>(M, k, 0, 0, nwg, P, winv + (int64_t)k * M.nb * M.nb, st);
 }
 
+// Trailing matrices of at most this many rows are factored in 64-wide steps
+// throughout (chol.hip): one launch of 23-40 us per step against a tile
+// step's chain of look-ahead, panel copy, panel solve and update.  Where the
+// rank-64 updates' memory traffic outweighs that: 2n = 6,400 at nb = 512,
+// whole evaluation, tiles from 4,096 rows 5.8 ms, from 6,144 5.3, from 8,192
+// 5.2; 2n = 12,800: 20.9, 20.3, 21.1 ms.
+constexpr int64_t FLAT_ROWS = 6144;
+
 // Right-looking tiled Cholesky with one tile of look-ahead.  Caller stream:
 // panel TRSM of column k (GEMM against W_k), then the trailing update of
 // step k except the diagonal tile (k+1, k+1).  Look-ahead stream: as soon as
@@ -831,6 +841,8 @@ int dense_potrf(mvg_mat *A, int64_t *d_info, hipStream_t st) {
     set_error("dense_potrf: matrix has no inverse-tile store");
     return MVG_ERR_STATE;
   }
+  const PivotTol pt = pivot_tol(A);
+  if (A->N <= FLAT_ROWS) return chol_flat(M, 0, dst_band, A->d_winv, d_info, pt, st);
   double *P = nullptr;
   const size_t pbytes = sizeof(double) * (size_t)std::max(1, T - 1) * M.nb * M.nb;
   if (malloc_async((void **)&P, pbytes, st) != hipSuccess) {
@@ -843,7 +855,6 @@ int dense_potrf(mvg_mat *A, int64_t *d_info, hipStream_t st) {
   hipEventCreateWithFlags(&evD, hipEventDisableTiming);
   hipEventCreateWithFlags(&evS, hipEventDisableTiming);
   hipEventCreateWithFlags(&ev0, hipEventDisableTiming);
-  const PivotTol pt = pivot_tol(A);
   int rc = 0;
   hipEventRecord(ev0, st);
   hipStreamWaitEvent(side, ev0, 0);
@@ -854,6 +865,11 @@ int dense_potrf(mvg_mat *A, int64_t *d_info, hipStream_t st) {
     rc = panel_trsm(step_map(k), k, A->d_winv, P, st);  // L_ik, i > k
     hipEventRecord(evS, st);
     if (rc) break;
+    if (k + 1 < T && A->N - (int64_t)(k + 1) * M.nb <= FLAT_ROWS) {
+      rc = trailing(step_map(k), A->N, k, false, false, st);
+      if (!rc) rc = chol_flat(M, k + 1, dst_band, A->d_winv, d_info, pt, st);
+      break;
+    }
     if (k + 1 < T) {
       hipStreamWaitEvent(side, evS, 0);
       rc = launch_syrk_next(A, k, side);  // SYRK of tile (k+1, k+1) by step k

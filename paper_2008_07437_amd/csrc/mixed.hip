@@ -593,6 +593,7 @@ static void mixed_flops(int64_t N, int nb, int T, int k, int band, double *f64, 
 int mixed_potrf(mvg_mat *A, int64_t *d_info, hipStream_t st) {
   const TileMap M = A->map();
   const int T = M.T, nb = M.nb, band = A->band;
+  if (band >= T) return dense_potrf(A, d_info, st);  // every tile is a band tile
   const bool bf16 = A->precision == MVG_MIXED_BF16;
   // BF16X3: as FP32X, with the off-band operands split into two BF16 terms
   const bool x3 = A->precision == MVG_MIXED_BF16X3;
@@ -627,7 +628,7 @@ int mixed_potrf(mvg_mat *A, int64_t *d_info, hipStream_t st) {
   int rc = 0;
   hipEventRecord(ev0, st);
   hipStreamWaitEvent(side, ev0, 0);
-  rc = diag_factor(M, 0, A->d_winv, d_info, pt, side);
+  rc = diag_factor_mixed(M, 0, A->d_winv, d_info, pt, side);
   hipEventRecord(evD, side);
   for (int k = 0; k < T && !rc; ++k) {
     hipStreamWaitEvent(st, evD, 0);
@@ -651,7 +652,7 @@ int mixed_potrf(mvg_mat *A, int64_t *d_info, hipStream_t st) {
     if (rc || k + 1 >= T) continue;
     hipStreamWaitEvent(side, evS, 0);
     rc = launch_syrk_next(A, k, side);
-    if (!rc) rc = diag_factor(M, k + 1, A->d_winv, d_info, pt, side);
+    if (!rc) rc = diag_factor_mixed(M, k + 1, A->d_winv, d_info, pt, side);
     hipEventRecord(evD, side);
     if (rc) break;
     hipLaunchKernelGGL(k_panel_stage_post, dim3((nb / 64) * (nb / 64), nbelow), dim3(256), 0, st,

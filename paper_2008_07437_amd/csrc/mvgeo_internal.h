@@ -87,6 +87,7 @@ struct TileMap {
   const int *kind;     // device array, TileKind per tile (nullptr: all F64)
   int T, nb;
   int iend;            // trailing updates touch tile rows < iend (T, or the DST band end)
+  int64_t stride = 0;  // bytes between packed tiles when every tile is FP64 (0: use off)
 };
 
 struct TlrState;
@@ -113,7 +114,11 @@ struct mvg_mat {
   mvg::MaternArgsP margs_p{};
   mvg::TlrState *tlr = nullptr;   // TLR storage (precision == MVG_TLR)
   mutable hipEvent_t done = nullptr;  // after the library's last asynchronous work on it
-  mvg::TileMap map() const { return mvg::TileMap{arena, d_off, d_kind, T, nb, T}; }
+  mvg::TileMap map() const {
+    const bool uniform = precision == MVG_FP64 || precision == MVG_MIXED_FP32X ||
+                         precision == MVG_MIXED_BF16X3;
+    return mvg::TileMap{arena, d_off, d_kind, T, nb, T, uniform ? (int64_t)nb * nb * 8 : 0};
+  }
 };
 
 struct mvg_factor {
@@ -164,6 +169,10 @@ int launch_trail(const TileMap &M, int k, int jlo, int64_t lid0, int64_t nwg, co
                  const double *W, hipStream_t st);
 int diag_factor(const TileMap &M, int k, double *winv, int64_t *d_info, const PivotTol &pt,
                 hipStream_t st);
+int diag_factor_mixed(const TileMap &M, int k, double *winv, int64_t *d_info, const PivotTol &pt,
+                      hipStream_t st);
+int chol_flat(const TileMap &M, int k, int band, double *winv, int64_t *d_info, const PivotTol &pt,
+              hipStream_t st);
 int launch_syrk_next(const mvg_mat *A, int k, hipStream_t st);
 int dense_potrf(mvg_mat *A, int64_t *d_info, hipStream_t st);
 int mixed_potrf(mvg_mat *A, int64_t *d_info, hipStream_t st);

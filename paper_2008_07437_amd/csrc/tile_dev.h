@@ -7,7 +7,8 @@
 namespace mvg {
 
 __device__ __forceinline__ double *tile_ptr(TileMap M, int I, int J) {
-  return reinterpret_cast<double *>(M.base + M.off[tidx(I, J, M.T)]);
+  const int64_t t = tidx(I, J, M.T);
+  return reinterpret_cast<double *>(M.base + (M.stride ? t * M.stride : M.off[t]));
 }
 __device__ __forceinline__ float *tile_ptr_f32(TileMap M, int I, int J) {
   return reinterpret_cast<float *>(M.base + M.off[tidx(I, J, M.T)]);

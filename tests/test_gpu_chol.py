@@ -1,0 +1,90 @@
+"""The 64-wide step factorisation against LAPACK and the oracle, at the edges
+of its blocks, tiles and of the size where the tiled factorisation takes over.
+
+Tolerances: the factor within 10x the difference of the oracle's and LAPACK's
+factors of the same matrix (1e-13 at least); L W = I through the solves, that
+is Eq. (1) within 1e-9 of the oracle."""
+import numpy as np
+import pytest
+import scipy.linalg
+
+import synthetic
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a HIP device")
+    import paper_2008_07437_amd as m
+    m._lib._load()
+    return m
+
+
+def _dev(a):
+    import torch
+    return torch.as_tensor(np.ascontiguousarray(a, dtype=np.float64)).cuda()
+
+
+def _sites(orc, n, seed):
+    x, y = synthetic.jittered_grid(n, seed)
+    p = orc.morton_order(x, y)
+    return x[p], y[p]
+
+
+# one and two rows past and before a 64-block, a tile, the last tile's padding
+@pytest.mark.parametrize("n,nb", [(1, 128), (31, 128), (32, 128), (33, 128), (63, 128), (64, 128),
+                                  (65, 256), (95, 256), (97, 256), (255, 512), (257, 512),
+                                  (383, 768), (385, 768), (513, 1024), (700, 1024)])
+def test_factor_block_edges(lib, orc, n, nb):
+    print("factor n=%d nb=%d" % (n, nb), flush=True)
+    th = (1.4, 0.6, 0.1, 0.7, 1.1, -0.4)
+    x, y = _sites(orc, n, 3)
+    A = lib.cov_generate(_dev(x), _dev(y), th, {"nb": nb})
+    assert lib.potrf_tiled(A) == 0
+    got = A.to_dense().cpu().numpy()
+    S = orc.cov_dense(x, y, th)
+    low, info = orc.potrf(S)
+    assert info == 0
+    floor = np.max(np.abs(low - scipy.linalg.cholesky(S, lower=True)))
+    assert np.max(np.abs(got - low)) <= max(10 * floor, 1e-13)
+    z = orc.simulate_z(x, y, th, synthetic.normal_eps(2 * n, 3))
+    ref = orc.loglik(x, y, z, th)
+    res, F = lib.loglik(_dev(x), _dev(y), _dev(z), th, {"nb": nb}, keep=True)
+    for key in ("loglik", "logdet", "quad"):
+        assert abs(res[key][0] - ref[key]) <= 1e-9 * max(abs(ref[key]), 1.0), key
+    w = F.w(n).cpu().numpy()  # W and W^T through both solves
+    np.testing.assert_allclose(S @ w, z, rtol=0, atol=1e-9 * np.max(np.abs(z)))
+
+
+# the tiled path, its last steps and the 64-wide tail on both sides of the switch
+@pytest.mark.parametrize("n,nb", [(3071, 128), (3072, 256), (3073, 512), (3100, 768), (3600, 1024)])
+def test_tiled_and_tail(lib, n, nb):
+    print("tiled n=%d nb=%d" % (n, nb), flush=True)
+    import torch
+    th = synthetic.THETA_REF
+    x, y = synthetic.jittered_grid(n, 4)
+    A = lib.cov_generate(_dev(x), _dev(y), th, {"nb": nb})
+    S = A.to_dense()
+    S = S + torch.tril(S, -1).T
+    assert lib.potrf_tiled(A) == 0
+    low = A.to_dense()
+    ref = torch.linalg.cholesky(S)
+    cpu = torch.as_tensor(scipy.linalg.cholesky(S.cpu().numpy(), lower=True)).cuda()
+    floor = float((ref - cpu).abs().max())
+    assert float((low - cpu).abs().max()) <= max(10 * floor, 1e-13)
+
+
+# a duplicated site: the failing pivot in the first, a middle and the last block
+@pytest.mark.parametrize("at", [1, 17, 40, 200, 299])
+def test_first_failing_pivot(lib, orc, at):
+    print("duplicate at %d" % at, flush=True)
+    x, y = _sites(orc, 300, 6)
+    x[at], y[at] = x[at - 1], y[at - 1]
+    z = np.ones(600)
+    ref = orc.loglik(x, y, z, synthetic.THETA_REF)
+    got = lib.loglik(_dev(x), _dev(y), _dev(z), synthetic.THETA_REF, {"nb": 128})
+    assert ref["info"] > 0 and got["status"][0] == ref["info"]
+    assert got["loglik"][0] == -np.inf

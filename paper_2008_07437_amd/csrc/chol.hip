@@ -19,12 +19,12 @@
 // Every block is written by one workgroup and all it reads was finished by
 // the launch before, so there is nothing to wait for inside a launch.
 //
-// Measured: 22 us a step while the chain bounds it (about 4 us of launch, 15
-// us of the 64 x 64 factor, the rest the products before it), 33 us at 4,096
-// trailing rows, where the rank-64 update's traffic does.  Before, a step
-// was three launches (factor 37 us, panel 5, update 9) and the inverse of a
-// tile 7 (nb = 512) or 15 more of 12 to 40 us each: 2n = 3,074 took 6.2 ms,
-// now 2.0; a 1024 tile 2 ms, now 0.4.
+// Measured: 18 us a step while the chain bounds it (about 4 us of launch, 1.3
+// of loads, 10 of the 64 x 64 factor, the rest the products before it), 33 us
+// at 4,096 trailing rows, where the rank-64 update's traffic does.  Before, a
+// step was three launches (factor 37 us, panel 5, update 9) and the inverse of
+// a tile 7 (nb = 512) or 15 more of 12 to 40 us each: 2n = 3,074 took 6.2 ms,
+// now 1.7; a 1024 tile 2 ms, now 0.3.
 #include <algorithm>
 #include <cmath>
 
@@ -210,6 +210,7 @@ static PivotRule pivot_rule(const PivotTol &pt, int64_t row0, int64_t plim) {
   for (int i = 0; i < PMAX; ++i) r.tol[i] = pt.tol[i];
   r.p = pt.p;
   r.row0 = row0;
+  r.m0 = (int)(row0 % pt.p);
   r.plim = plim;
   return r;
 }

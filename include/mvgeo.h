@@ -132,7 +132,7 @@ int potrf_tiled(mvg_mat *A, const mvg_opts *o, int64_t *h_info, void *hip_stream
  * d_z: 2*n_loc FP64 in Representation I.  Host outputs (n_theta each):
  * h_loglik, h_logdet, h_quad (nullable), h_status (nullable: 0 or the pivot
  * index; a failing theta gets h_loglik = -inf).  n_theta > 1 evaluates all
- * theta on the same arena (large problems) or in one persistent launch
+ * theta on the same arena (large problems) or all together
  * (2 n_loc <= MVG_SMALL_MAX_ROWS, FP64, see loglik_many).  keep (nullable, n_theta == 1 only) receives a resident factor for
  * cokrige_predict.  Returns 0, -1..-12 for bad arguments, MVG_ERR_*.
  *
@@ -320,9 +320,9 @@ typedef struct {
 #define MVG_SMALL_MAX_ROWS 1024
 
 /* Eq. (1) for many small problems (2 n_loc <= MVG_SMALL_MAX_ROWS each,
- * datasets and theta may all differ) in one persistent launch: a fixed grid
- * of workgroups takes tasks from a device queue, one workgroup per task
- * (generation, FP64 Cholesky, solve, log-determinant).  A task's result does
+ * datasets and theta may all differ): the tasks advance together, one launch
+ * per 64 columns of all of them, several workgroups per task (generation,
+ * FP64 Cholesky, solve, log-determinant).  A task's result does
  * not depend on the other tasks of the batch (bitwise).  loglik with
  * n_theta > 1, FP64 and 2 n_loc <= MVG_SMALL_MAX_ROWS (and no keep) takes
  * this path.  Outputs as for loglik (host, n_tasks each; h_logdet, h_quad,
@@ -340,11 +340,11 @@ int loglik_many(const mvg_task *h_tasks, int n_tasks, double *h_loglik, double *
 /* loglik_many without any allocation, for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  Same tasks, outputs and results
- * (bitwise) as loglik_many; the task list, per-task outputs, queue counter
- * and per-workgroup workspaces live in the library's fixed scratch array of
+ * (bitwise) as loglik_many; the task list, per-task outputs and
+ * workspaces live in the library's fixed scratch array of
  * MVG_NOALLOC_SCRATCH_BYTES on the current device instead of an allocation
- * (when it holds fewer N x N workspaces than loglik_many would allocate,
- * fewer workgroups take the same tasks).  The call stages through static
+ * (when it holds fewer workspaces than loglik_many would allocate, the
+ * tasks go in groups).  The call stages through static
  * host buffers and synchronises hip_stream before it returns.  Calls from
  * one process are serialised; calls from several processes that overlap on
  * one GPU would share its array and race (there is no cross-process lock).
@@ -422,7 +422,7 @@ void mvg_factor_destroy(mvg_factor *F);
  * and cokriging requests of uneven size are admitted by HBM footprint
  * (mvg_footprint) against a byte budget and run concurrently on n_workers
  * streams; small FP64 likelihoods waiting together are evaluated in one
- * persistent launch (loglik_many); factors stay resident in an LRU cache
+ * batch (loglik_many); factors stay resident in an LRU cache
  * keyed by (dataset, theta) and serve later cokriging requests (a miss
  * factors first).  Results (mvg_result) carry the server-clock arrival,
  * start and end times.  Datasets and cokriging buffers are caller-owned

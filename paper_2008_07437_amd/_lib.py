@@ -413,7 +413,7 @@ SMALL_MAX_ROWS = 1024
 
 
 def loglik_many(tasks, stream=None, noalloc=False):
-    """Eq. (1) for many small problems in one persistent launch.  tasks: list
+    """Eq. (1) for many small problems together.  tasks: list
     of (x, y, z, theta) with device float64 tensors (2 n <= 1024).  Returns a
     dict of numpy arrays as loglik does.  noalloc=True calls
     loglik_many_noalloc (the library's fixed scratch array, no allocation)."""

@@ -1,442 +1,272 @@
-// Many small likelihoods in one persistent launch (Eq. 1 per task).
+// Many small likelihoods at once (Eq. 1 per task).
 //
-// Each task is one (dataset, theta) pair with 2n <= SMALL_MAX rows.  A fixed
-// grid of workgroups pulls task indices from a device counter until the list
-// is exhausted; a workgroup evaluates its task alone: the per-theta
-// quadrature table in LDS, the lower triangle of Sigma in its private
-// workspace, a left-looking Cholesky in column blocks of SB (each block
-// column first receives all earlier columns' updates on FP64 MFMA, then its
-// diagonal block is factored by one wave in registers with its inverse and
-// the rows below are solved by that inverse on MFMA), the forward solve
-// folded into the factorisation,
-// and the log-determinant and quadratic form summed in a fixed order.  A task's
-// arithmetic does not depend on which workgroup runs it or on the other
-// tasks, so results are the same alone and in any batch.
+// Each task is one (dataset, theta) pair with 2n <= SMALL_MAX rows, padded to
+// 64-row blocks (identity).  All tasks of a group advance together, one
+// launch per 64 columns: a launch gives every task the workgroups of its step
+// (several per task, so that a few tasks fill the chip as well as many do),
+// and what a workgroup reads was finished by the launch before.  Left-looking
+// by 64-block columns, so that a block of L is read, not read and written,
+// once per later column:
+//
+//   launch t:  rows R > t + 1:  L(R, t) = (A(R, t) - sum_{m<t} L(R, m) L(t, m)^T)
+//                                         W(t, t)^T
+//              row t + 1:       the same; its sums over m < t - 1 were formed
+//                               ahead by the launch before, so the serial chain
+//                               (row, diagonal block, 64 x 64 factor) has the
+//                               same length at every step
+//              ahead:           A(t+2, t+1) and A(t+2, t+2) -= their sums over m < t
+//
+// The forward solve rides along (v_R -= L(R, t) y_t beside each row block) and
+// a last launch per task sums the log-determinant and the quadratic form in a
+// fixed order.  A task's arithmetic depends on its own data alone, so results
+// are the same alone and in any batch.
+//
+// Bound by the FP64 matrix units and, with few tasks, by the chain of steps.
+// Measured against one workgroup per task in a persistent launch: 1024 theta
+// at n = 400 12.7 -> 9.6 ms (4.0 of it generation; steps at 50 % MFMA busy, 8
+// GB read), 192 tasks of n = 20..512 7.3 -> 2.0 ms (the largest task's latency
+// on its one workgroup had set it).
+#include <algorithm>
 #include <cmath>
 
+#include "chol_dev.h"
 #include "matern_dev.h"
 
 namespace mvg {
 
-constexpr int SB = 32;             // column block
-constexpr int SW = 4;              // waves per workgroup (two workgroups per CU)
-constexpr int STHREADS = 64 * SW;
+constexpr int SMALL_GROUP = 1024;  // tasks that advance together at most
 
-typedef double dbl4s __attribute__((ext_vector_type(4)));
+__host__ __device__ inline int small_blocks(int64_t n) { return (int)((2 * n + CB - 1) / CB); }
 
-// A[col * N + row] from a clamped address inside the task's N x N workspace.
-// Masked entries are loaded unconditionally and zeroed afterwards, behind a
-// scheduling barrier: a load under a branch, or a select scheduled next to
-// its load, waits for the value at once, and a wave's loads then go out one
-// at a time instead of all in flight together.
-// The offset is formed in 32 bits (the workspace of one task is below 4 GiB)
-// so that the load takes the uniform base in scalar registers.
-__device__ __forceinline__ double clamped_load(const double *A, int N, int col, int row) {
-  const unsigned off = ((unsigned)min(col, N - 1) * (unsigned)N + (unsigned)min(row, N - 1)) * 8u;
-  return *(const double *)((const char *)A + off);
-}
-
-__device__ __forceinline__ double load_at(const double *A, int N, int col, int row) {
-  return *(const double *)((const char *)A + ((unsigned)col * (unsigned)N + (unsigned)row) * 8u);
-}
-
-__device__ __forceinline__ void store_at(double *A, int N, int col, int row, double v) {
-  *(double *)((char *)A + ((unsigned)col * (unsigned)N + (unsigned)row) * 8u) = v;
-}
-
-// x of lane l (l uniform) as a uniform value
-__device__ __forceinline__ double readlane_d(double x, int l) {
-  const long long b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_readlane((int)b, l);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
-// Sum of x over the 16 lanes of a DPP row (lanes 16 g .. 16 g + 15), in lane
-// 16 g: pairs, quads, halves of the row (lane i with 7 - i), then the row
-// mirrored (lane i with 15 - i).
-template <int CTRL>
-__device__ __forceinline__ double dpp_d(double x) {
-  const long long b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-__device__ __forceinline__ double row16_sum(double x) {
-  x += dpp_d<0xB1>(x);   // quad_perm [1, 0, 3, 2]
-  x += dpp_d<0x4E>(x);   // quad_perm [2, 3, 0, 1]
-  x += dpp_d<0x141>(x);  // row_half_mirror
-  x += dpp_d<0x140>(x);  // row_mirror
-  return x;
-}
-
-// Left-looking update of the columns k0 .. k0 + kb - 1 (kb <= 16 NT), rows
-// k0 .. N - 1, by the columns q in [qlo, k0): A[r][c] -= sum_q L[r][q] L[c][q],
-// on FP64 MFMA.  The rows are cut into 32-row output blocks, one per wave
-// (2 x NT tiles of 16 x 16: lane j + 16 (i % 4), element i / 4 of a tile);
-// when there are fewer blocks than waves, the q range of a block is split over
-// several waves and their partial tiles are summed in a fixed order through
-// the workgroup's scratch.  The block columns are updated two at a time
-// (NT = 4: 64 columns by every earlier column, then the second block of the
-// pair by the first one alone, NT = 2), so the panels L[., < k0] are read once
-// per 64 columns: about a sixth of the bytes of a right-looking update, which
-// reads and writes the trailing matrix at every step.  Every load is from a
-// clamped address inside the task's N x N workspace, masked after the load;
-// the next 16 columns' operands are in flight while the current ones feed
-// the MFMAs.  Outputs above the diagonal (the first row block of the second
-// block of a pair) are computed and stored like the others and never read.
-template <int NT>
-__device__ __forceinline__ void left_update(double *A, int N, int k0, int kb, int qlo,
-                                            double *part, int wave, int lane, int tid) {
-  constexpr int BW = 16 * NT;  // output columns of a block
-  const int l16 = lane & 15, lk = lane >> 4;
-  const int nout = (N - k0 + 31) / 32;
-  const int splits = nout >= SW ? 1 : SW / nout;
-  const int nitems = nout * splits;
-  const int K = k0 - qlo;
-  const int kc = (K / splits + 7) / 8 * 8;  // q per part (a multiple of 8)
-  for (int it = wave; it < nitems; it += SW) {
-    const int b = it / splits, pt = it % splits;
-    const int iA = k0 + 32 * b;
-    const int q0 = qlo + min(K, pt * kc), q1 = qlo + min(K, pt * kc + kc);
-    dbl4s acc[2][NT];
-#pragma unroll
-    for (int hi = 0; hi < 2; ++hi)
-#pragma unroll
-      for (int hj = 0; hj < NT; ++hj)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          acc[hi][hj][e] = pt == 0 ? clamped_load(A, N, k0 + 16 * hj + l16, iA + 16 * hi + 4 * e + lk)
-                                   : 0.0;
-    double ca[2][2], cb[NT][2];  // [h][kk]: rows 16 h + l16, columns q + 4 kk + lk
-    auto fetch = [&](int q, double (&fa)[2][2], double (&fb)[NT][2]) {
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) fa[h][kk] = clamped_load(A, N, q + 4 * kk + lk, iA + 16 * h + l16);
-#pragma unroll
-        for (int h = 0; h < NT; ++h) fb[h][kk] = clamped_load(A, N, q + 4 * kk + lk, k0 + 16 * h + l16);
-      }
-    };
-    // two chunks of 8 columns in flight ahead of the one feeding the MFMAs
-    // (addresses clamped to the last column; chunks past q1 are not used)
-    double ma[2][2], mb[NT][2];
-    if (q0 < q1) {
-      fetch(q0, ca, cb);
-      fetch(min(q0 + 8, q1 - 1), ma, mb);
-    }
-    for (int q = q0; q < q1; q += 8) {
-      double na[2][2], nb2[NT][2];
-      fetch(min(q + 16, q1 - 1), na, nb2);
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        const bool okq = q + 4 * kk + lk < q1;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) ca[h][kk] = (okq && iA + 16 * h + l16 < N) ? -ca[h][kk] : 0.0;
-#pragma unroll
-        for (int h = 0; h < NT; ++h)
-          if (!(okq && 16 * h + l16 < kb)) cb[h][kk] = 0.0;
-      }
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-        for (int hi = 0; hi < 2; ++hi)
-#pragma unroll
-          for (int hj = 0; hj < NT; ++hj)
-            acc[hi][hj] = __builtin_amdgcn_mfma_f64_16x16x4f64(ca[hi][kk], cb[hj][kk], acc[hi][hj], 0, 0, 0);
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          ca[h][kk] = ma[h][kk];
-          ma[h][kk] = na[h][kk];
-        }
-#pragma unroll
-        for (int h = 0; h < NT; ++h) {
-          cb[h][kk] = mb[h][kk];
-          mb[h][kk] = nb2[h][kk];
-        }
-      }
-    }
-#pragma unroll
-    for (int hi = 0; hi < 2; ++hi)
-#pragma unroll
-      for (int hj = 0; hj < NT; ++hj)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = 16 * hi + 4 * e + lk, c = 16 * hj + l16;
-          if (splits == 1) {
-            if (iA + r < N && c < kb) store_at(A, N, k0 + c, iA + r, acc[hi][hj][e]);
-          } else {
-            part[(int64_t)wave * (32 * BW) + c * 32 + r] = acc[hi][hj][e];
-          }
-        }
+// One task's workspace: lower 64 x 64 blocks of the matrix (column-major
+// inside, rows of blocks one after another), inverses of the diagonal blocks,
+// right-hand side, solution, quadrature table, pivot info.
+struct SmallSlot {
+  double *base;
+  int nk;
+  __device__ double *blk(int R, int C) const { return base + (int64_t)(R * (R + 1) / 2 + C) * CB * CB; }
+  __device__ double *inv(int k) const {
+    return base + (int64_t)(nk * (nk + 1) / 2 + k) * CB * CB;
   }
-  if (splits > 1) {  // item it ran on wave it (nitems <= SW)
-    __syncthreads();
-    for (int e = tid; e < nout * 32 * BW; e += STHREADS) {
-      const int b = e / (32 * BW), idx = e % (32 * BW), r = idx % 32, c = idx / 32;
-      double t = 0.0;
-      for (int p = 0; p < splits; ++p) t += part[(int64_t)(b * splits + p) * (32 * BW) + idx];
-      if (k0 + 32 * b + r < N && c < kb) store_at(A, N, k0 + c, k0 + 32 * b + r, t);
-    }
-  }
-}
-
-// Two workgroups per CU (at most 256 registers per lane): one task's
-// generation (FP64 VALU) runs beside another's factorisation (MFMA, memory).
-__global__ __launch_bounds__(STHREADS) __attribute__((amdgpu_waves_per_eu(2))) void k_small_loglik(
-    const SmallTask *__restrict__ tasks, int ntask, int *__restrict__ counter,
-    double *__restrict__ ws_all, int64_t ws_stride, double *__restrict__ out) {
-  __shared__ double sq[4 * QN];
-  __shared__ double sW[SB][SB + 1];   // W = L_kk^-1
-  __shared__ double sy[SB];
-  __shared__ double slg[SB];          // log L_jj of the block
-  __shared__ double szk[SB];          // z of the block's rows
-  __shared__ int s_task, s_fail;
-  __shared__ double s_logdet, s_quad;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  double *ws = ws_all + (int64_t)blockIdx.x * ws_stride;
-  for (;;) {
-    if (tid == 0) s_task = atomicAdd(counter, 1);
-    __syncthreads();
-    const int ti = s_task;
-    __syncthreads();
-    if (ti >= ntask) break;
-    const SmallTask tk = tasks[ti];
-    const int n = (int)tk.n, N = 2 * n;
-    double *A = ws;          // N x N, column-major, ld N (lower triangle used)
-    double *zv = ws + (int64_t)N * N;  // right-hand side being solved
-    double *part = zv + N;   // SW partial 32 x 64 tiles of the split updates
-    // quadrature table
-    for (int k = tid; k < QN; k += STHREADS) quad_entry(k, tk.P, sq);
-    for (int i = tid; i < N; i += STHREADS) zv[i] = tk.z[i];
-    if (tid == 0) {
-      s_fail = 0;
-      s_logdet = 0.0;
-      s_quad = 0.0;
-    }
-    __syncthreads();
-    // Sigma: 2 x 2 blocks of the n (n + 1) / 2 location pairs l >= r, spread
-    // evenly over the threads.  Column r of the pairs (l = r .. n - 1) and
-    // column n - 1 - r together hold n + 1 pairs, so pair p is entry p % (n + 1)
-    // of folded row p / (n + 1) (for odd n the middle column is the last,
-    // half-filled row); a thread steps its (row, entry) by STHREADS pairs.
-    const int npair = n * (n + 1) / 2, wf = n + 1;
-    int fi = tid / wf, fc = tid % wf;
-    for (int pq = tid; pq < npair; pq += STHREADS) {
-      const bool first = fc < n - fi;
-      const int r = first ? fi : n - 1 - fi;
-      const int l = first ? fi + fc : r + (fc - (n - fi));
-      double c[3];
-      cross_cov_block(tk.x[l], tk.y[l], tk.x[r], tk.y[r], tk.P, sq, c);
-      double *a = A + (int64_t)(2 * r) * N + 2 * l;
-      a[0] = c[0];
-      a[1] = c[2];
-      a[N] = c[2];
-      a[N + 1] = c[1];
-      fc += STHREADS;
-      while (fc >= wf) {
-        fc -= wf;
-        ++fi;
-      }
-    }
-    __syncthreads();
-    for (int k0 = 0; k0 < N; k0 += SB) {
-      const int kb = min(SB, N - k0);
-      // (u) this block column receives all earlier columns' updates at once
-      // (two at a time: the first block of a pair takes every earlier
-      // column for both blocks, the second then only the first's columns)
-      if (k0 > 0) {
-        if ((k0 / SB) % 2 == 0)
-          left_update<2 * SB / 16>(A, N, k0, min(2 * SB, N - k0), 0, part, wave, lane, tid);
-        else
-          left_update<SB / 16>(A, N, k0, kb, k0 - SB, part, wave, lane, tid);
-        __syncthreads();
-      }
-      // (a) diagonal block by wave 0 in registers, without workgroup
-      // barriers: lane r holds row r of the block (lanes 32..63 the same rows;
-      // only lanes < 32 write).  Column c's pivot and entries come from their
-      // lanes as uniform values (readlane); then W = L_kk^-1, column c by lane
-      // c, and L_kk back to A.  The arithmetic per entry is that of a
-      // column-by-column Cholesky and a forward substitution per column.
-      if (wave == 0) {
-        const int rr = lane & 31;
-        const bool wl = lane < 32;
-        double a[SB];
-#pragma unroll
-        for (int c = 0; c < SB; ++c) a[c] = clamped_load(A, N, k0 + c, k0 + rr);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int c = 0; c < SB; ++c)
-          if (!(c <= rr && rr < kb)) a[c] = 0.0;
-        if (wl && lane < kb) szk[lane] = zv[k0 + lane];  // final: earlier blocks have updated it
-        int fail = 0;
-#pragma unroll
-        for (int c = 0; c < SB; ++c) {
-          if (fail || c >= kb) continue;  // uniform (no break: the loop stays unrolled)
-          const double d = readlane_d(a[c], c);
-          const int g = k0 + c;
-          const double tol = (g & 1) ? tk.t1 : tk.t0;
-          if (!(d > tol) || !(d > 0.0)) {  // uniform
-            fail = g + 1;
-            continue;
-          }
-          const double ljj = sqrt(d);
-          a[c] = rr == c ? ljj : (rr > c ? a[c] / ljj : a[c]);
-#pragma unroll
-          for (int q = c + 1; q < SB; ++q) a[q] -= a[c] * readlane_d(a[c], q);  // rows q <= rr used
-        }
-        if (fail) {
-          if (lane == 0) s_fail = fail;
-        } else {
-          double dg = 0.0;  // this lane's L_rr (static register indices)
-#pragma unroll
-          for (int q = 0; q < SB; ++q)
-            if (q == rr) dg = a[q];
-          if (wl && lane < kb) slg[lane] = log(dg);
-          // column c of W by lane c (rows above c are zeros, so the sums over
-          // q < c add exact zeros); entries outside the kb x kb block are zero
-          const int c = rr;
-          double w[SB];
-#pragma unroll
-          for (int r = 0; r < SB; ++r) {
-            // (the right-hand side e_c enters as the 1 at r = c, where the sum
-            // is over zeros: no per-lane constant held across the task loop)
-            double sacc = 0.0;
-#pragma unroll
-            for (int q = 0; q < r; ++q) sacc -= readlane_d(a[q], r) * w[q];
-            w[r] = (r >= c && r < kb) ? (r == c ? 1.0 : sacc) / readlane_d(a[r], r) : 0.0;
-          }
-          if (wl) {
-#pragma unroll
-            for (int r = 0; r < SB; ++r) sW[r][c] = w[r];
-            // L_kk back to A (the solve of later columns does not need it)
-            if (rr < kb)
-#pragma unroll
-              for (int q = 0; q < SB; ++q)
-                if (q <= rr) A[(int64_t)(k0 + q) * N + k0 + rr] = a[q];
-          }
-        }
-      }
-      __syncthreads();
-      if (s_fail) break;
-      if (tid == 0) {
-        double ld = s_logdet;
-        for (int c = 0; c < kb; ++c) ld += slg[c];
-        s_logdet = ld;
-      }
-      if (tid < SB) {
-        double s = 0.0;
-#pragma unroll
-        for (int q = 0; q < SB; ++q)
-          if (q <= tid && q < kb) s += sW[tid][q] * szk[q];
-        sy[tid] = tid < kb ? s : 0.0;
-      }
-      __syncthreads();
-      if (tid == 0) {
-        double q = s_quad;
-        for (int c = 0; c < kb; ++c) q += sy[c] * sy[c];
-        s_quad = q;
-      }
-      // (b) panel rows i >= k0 + kb: L_i = A_i W^T on MFMA, 16 rows per wave
-      //     (a wave reads its rows' A values before it overwrites them), and
-      //     the solve's z_i -= L_i y_k from the same accumulators (a row's 16
-      //     columns of a half are in the 16 lanes of one DPP row)
-      //     W's fragments are the same for every tile (registers); the next
-      //     tile's A values are in flight while this one's feed the MFMAs
-      const int r0 = k0 + kb;
-      const int l16 = lane & 15, lk = lane >> 4;
-      const int ntile = (N - r0 + 15) / 16;
-      double wf[SB / 16][SB / 4];
-#pragma unroll
-      for (int half = 0; half < SB / 16; ++half)
-#pragma unroll
-        for (int kk = 0; kk < SB / 4; ++kk) wf[half][kk] = sW[half * 16 + l16][4 * kk + lk];
-      double avn[SB / 4];
-#pragma unroll
-      for (int kk = 0; kk < SB / 4; ++kk)
-        avn[kk] = clamped_load(A, N, k0 + 4 * kk + lk, r0 + wave * 16 + l16);
-      for (int t = wave; t < ntile; t += SW) {
-        const int row = r0 + t * 16 + l16;
-        double av[SB / 4];
-#pragma unroll
-        for (int kk = 0; kk < SB / 4; ++kk) {
-          av[kk] = avn[kk];
-          avn[kk] = clamped_load(A, N, k0 + 4 * kk + lk, row + 16 * SW);  // next tile (clamped)
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int kk = 0; kk < SB / 4; ++kk)
-          if (!(row < N && 4 * kk + lk < kb)) av[kk] = 0.0;
-        double zp[4] = {0.0, 0.0, 0.0, 0.0};  // rows 4 e + lk of the tile
-#pragma unroll
-        for (int half = 0; half < SB / 16; ++half) {
-          dbl4s acc = dbl4s{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-          for (int kk = 0; kk < SB / 4; ++kk)
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av[kk], wf[half][kk], acc, 0, 0, 0);
-          const int c = half * 16 + l16;
-          const double yc = sy[c];  // zero for c >= kb
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int gi = r0 + t * 16 + 4 * e + lk;
-            if (gi < N && c < kb) A[(int64_t)(k0 + c) * N + gi] = acc[e];
-            zp[e] += acc[e] * yc;
-          }
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const double zs = row16_sum(zp[e]);
-          const int gi = r0 + t * 16 + 4 * e + lk;
-          if (l16 == 0 && gi < N) zv[gi] -= zs;
-        }
-      }
-      __syncthreads();
-    }    if (tid == 0) {
-      double *o = out + 4 * (int64_t)ti;
-      if (s_fail) {
-        o[0] = -INFINITY;
-        o[1] = NAN;
-        o[2] = NAN;
-        o[3] = (double)s_fail;
-      } else {
-        const double logdet = 2.0 * s_logdet, quad = s_quad;
-        o[0] = -(double)n * log(2.0 * M_PI) - 0.5 * logdet - 0.5 * quad;
-        o[1] = logdet;
-        o[2] = quad;
-        o[3] = 0.0;
-      }
-    }
-    __syncthreads();
-  }
-}
-
-__global__ void k_zero_int(int *p) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *p = 0;
-}
-
-int small_batch_workgroups(int ntask) { return ntask < 2 * 256 ? ntask : 2 * 256; }
+  __device__ double *v() const { return inv(nk); }
+  __device__ double *y() const { return v() + CB * nk; }
+  __device__ double *qtab() const { return y() + CB * nk; }
+  __device__ int64_t *info() const { return reinterpret_cast<int64_t *>(qtab() + 4 * QN); }
+};
 
 size_t small_workspace_doubles(int64_t nmax) {
-  const int64_t N = 2 * nmax;
-  return (size_t)(N * N + N + SW * SB * 2 * SB);  // matrix, right-hand side, split partials
+  const size_t k = small_blocks(nmax);
+  return (k * (k + 1) / 2 + k) * CB * CB + 2 * CB * k + 4 * QN + 32;
 }
 
-int launch_small_loglik(const SmallTask *d_tasks, int ntask, int64_t nmax, int *d_counter,
-                        double *d_ws, double *d_out, hipStream_t st, int max_wg) {
+int small_batch_slots(int ntask) { return std::min(ntask, SMALL_GROUP); }
+
+// Workgroup index b of a list of ntask x per workgroups, the tasks dealt to
+// the XCDs (workgroups go to them round robin), so that a task's workgroups
+// share one L2.
+__device__ __forceinline__ bool task_of(int b, int ntask, int per, int &task, int &item) {
+  const int q = b >> 3;
+  task = q / per * 8 + (b & 7);
+  item = q % per;
+  return task < ntask;
+}
+
+__global__ __launch_bounds__(256) void k_small_prep(const SmallTask *__restrict__ tasks, double *ws,
+                                                    int64_t stride) {
+  const SmallTask &tk = tasks[blockIdx.x];
+  const SmallSlot s{ws + (int64_t)blockIdx.x * stride, small_blocks(tk.n)};
+  for (int k = threadIdx.x; k < QN; k += 256) quad_entry(k, tk.P, s.qtab());
+  const int N = 2 * (int)tk.n;
+  for (int i = threadIdx.x; i < CB * s.nk; i += 256) s.v()[i] = i < N ? tk.z[i] : 0.0;
+  if (threadIdx.x == 0) *s.info() = INT64_MAX;
+}
+
+// One 64 x 64 block of Sigma (32 x 32 location pairs) per workgroup: bound by
+// the quadrature's FP64 arithmetic, the block is written once.
+__global__ __launch_bounds__(256) void k_small_cov(const SmallTask *__restrict__ tasks, int ntask,
+                                                   double *ws, int64_t stride, int per) {
+  __shared__ double sq[4 * QN];
+  int task, item;
+  if (!task_of(blockIdx.x, ntask, per, task, item)) return;
+  const SmallTask &tk = tasks[task];
+  const SmallSlot s{ws + (int64_t)task * stride, small_blocks(tk.n)};
+  if (item >= s.nk * (s.nk + 1) / 2) return;
+  for (int i = threadIdx.x; i < 4 * QN; i += 256) sq[i] = s.qtab()[i];
+  __syncthreads();
+  int R = (int)((sqrtf(8.0f * (float)item + 1.0f) - 1.0f) * 0.5f);
+  while ((R + 1) * (R + 2) / 2 <= item) ++R;
+  while (R * (R + 1) / 2 > item) --R;
+  const int C = item - R * (R + 1) / 2, n = (int)tk.n;
+  const int pl = threadIdx.x & 31, gl = 32 * R + pl;
+  const double xl = gl < n ? tk.x[gl] : 0.0, yl = gl < n ? tk.y[gl] : 0.0;
+  double *B = s.blk(R, C) + 2 * pl;
+  const MaternArgs P = tk.P;
+  for (int q = 0; q < 4; ++q) {
+    const int pr = (threadIdx.x >> 5) * 4 + q, gr = 32 * C + pr;
+    double c[3];
+    if (gl >= n || gr >= n) {
+      c[0] = c[1] = gl == gr ? 1.0 : 0.0;
+      c[2] = 0.0;
+    } else {
+      cross_cov_block(xl, yl, tk.x[gr], tk.y[gr], P, sq, c);
+    }
+    *reinterpret_cast<double2 *>(B + 2 * pr * CB) = make_double2(c[0], c[2]);
+    *reinterpret_cast<double2 *>(B + (2 * pr + 1) * CB) = make_double2(c[2], c[1]);
+  }
+}
+
+// acc (16 rows of block row R per wave, row layout) -= sum_{m<nm} L(R, m)
+// L(C, m)^T: the C blocks go through LDS, two in turn, one barrier each, the
+// next pair of blocks in flight under the products.
+__device__ __forceinline__ void left_sum(Rows &acc, const double *LR, const double *LC, int nm,
+                                         double *sm) {
+  if (nm <= 0) return;
+  double v[16];
+  Rows a;
+  block_load(LC, CB, v);
+  rows_load(LR, CB, a);
+  for (int m = 0; m < nm; ++m) {
+    double *b = sm + (m & 1) * CB * CB;
+    const Rows c = a;
+    block_store(b, v);
+    __syncthreads();
+    const int64_t nx = (int64_t)min(m + 1, nm - 1) * CB * CB;
+    block_load(LC + nx, CB, v);
+    rows_load(LR + nx, CB, a);
+    rows_sub_nt(acc, c, b, 4);
+  }
+}
+
+// Log-determinant, quadratic form and Eq. (1) of a factored task.
+__device__ __forceinline__ void small_finish(const SmallSlot &s, int n, double *sm, double *o) {
+  const int tid = threadIdx.x, last = s.nk - 1;
+  double *part = sm + 2 * CB * CB, *r0 = sm, *r1 = sm + 256;
+  double v[16];
+  block_load(s.inv(last), CB, v);
+  block_store(sm, v);
+  __syncthreads();
+  solve_parts(sm, s.v() + CB * last, part);
+  __syncthreads();
+  double ld = 0.0, q = 0.0;
+  for (int i = tid; i < CB * s.nk; i += 256) {
+    const int k = i / CB, r = i % CB;
+    const double y = k == last ? solve_y(part, r) : s.y()[i];
+    ld += log(s.blk(k, k)[r * CB + r]);  // padding rows: log 1, y = 0
+    q += y * y;
+  }
+  r0[tid] = ld;
+  r1[tid] = q;
+  __syncthreads();
+  for (int h = 128; h > 0; h >>= 1) {
+    if (tid < h) {
+      r0[tid] += r0[tid + h];
+      r1[tid] += r1[tid + h];
+    }
+    __syncthreads();
+  }
+  if (tid == 0) {
+    const int64_t fail = *s.info();
+    const double logdet = 2.0 * r0[0], quad = r1[0];
+    const bool ok = fail == INT64_MAX;
+    o[0] = ok ? -(double)n * log(2.0 * M_PI) - 0.5 * logdet - 0.5 * quad : -INFINITY;
+    o[1] = ok ? logdet : NAN;
+    o[2] = ok ? quad : NAN;
+    o[3] = ok ? 0.0 : (double)fail;
+  }
+}
+
+// Step t of every task: first each task's row t + 1 (the serial chain) or, at
+// its end, its sums; then the other rows and the two blocks ahead.
+__global__ __launch_bounds__(256, 2) void k_small_step(const SmallTask *__restrict__ tasks, int ntask,
+                                                       double *ws, int64_t stride, int t, int per,
+                                                       double *__restrict__ out) {
+  __shared__ double sm[CHOL_LDS];
+  int b = blockIdx.x;
+  if (b < ntask) {
+    const SmallTask &tk = tasks[b];
+    const SmallSlot s{ws + (int64_t)b * stride, small_blocks(tk.n)};
+    if (t + 1 < s.nk) {
+      RowStep r{};
+      r.ld = r.ldw = CB;
+      r.S = s.blk(t + 1, t + 1);
+      r.Wn = s.inv(t + 1);
+      if (t >= 0) {
+        r.A1 = s.blk(t + 1, t);
+        r.Wt = s.inv(t);
+        r.vt = s.v() + CB * t;
+        r.vr = s.v() + CB * (t + 1);
+        r.yt = s.y() + CB * t;
+        if (t > 0) {
+          r.P1 = s.blk(t + 1, t - 1);
+          r.P0 = s.blk(t, t - 1);
+        }
+      }
+      PivotRule pr{};
+      pr.tol[0] = tk.t0;
+      pr.tol[1] = tk.t1;
+      pr.p = 2;
+      pr.plim = 2 * tk.n;
+      row_step<true, true>(r, sm, (int64_t)(t + 1) * CB, pr, s.info());
+    } else if (t + 1 == s.nk) {
+      small_finish(s, (int)tk.n, sm, out + 4 * (int64_t)b);
+    }
+    return;
+  }
+  int task, item;
+  if (!task_of(b - ntask, ntask, per, task, item)) return;
+  const SmallSlot s{ws + (int64_t)task * stride, small_blocks(tasks[task].n)};
+  if (item < 2) {  // ahead: (t + 2, t + 1), (t + 2, t + 2)
+    const int R = t + 2, C = t + 1 + item;
+    if (R >= s.nk || t < 1) return;
+    Rows acc;
+    rows_load(s.blk(R, C), CB, acc);
+    left_sum(acc, s.blk(R, 0), s.blk(C, 0), t, sm);
+    rows_store(s.blk(R, C), CB, acc);
+    return;
+  }
+  const int R = t + item;  // rows t + 2 on
+  if (R >= s.nk) return;
+  Rows acc, x;
+  double v[16];
+  double *w = sm + (t & 1) * CB * CB, *part = sm + 2 * CB * CB;
+  rows_load(s.blk(R, t), CB, acc);
+  block_load(s.inv(t), CB, v);  // in flight under the sum
+  left_sum(acc, s.blk(R, 0), s.blk(t, 0), t, sm);
+  block_store(w, v);  // the buffer that the last product did not read
+  __syncthreads();
+  solve_parts(w, s.v() + CB * t, part);
+  rows_mul_wt(x, acc, w);
+  rows_store(s.blk(R, t), CB, x);
+  __syncthreads();
+  solve_rows(x, part, part + 16 * CT + (threadIdx.x >> 6) * CB, s.v() + CB * R);
+}
+
+int launch_small_loglik(const SmallTask *d_tasks, const SmallTask *h_tasks, int ntask, int64_t nmax,
+                        double *d_ws, int slots, double *d_out, hipStream_t st) {
   if (ntask <= 0) return 0;
-  if (2 * nmax > SMALL_MAX) {
+  if (2 * nmax > SMALL_MAX || slots < 1) {
     set_error("batched small likelihood: 2n = %lld above %d", (long long)(2 * nmax), SMALL_MAX);
     return MVG_ERR_LIMIT;
   }
-  hipLaunchKernelGGL(k_zero_int, dim3(1), dim3(64), 0, st, d_counter);
-  if (int rc = check_launch("zero_int")) return rc;
-  int G = small_batch_workgroups(ntask);
-  if (max_wg > 0 && G > max_wg) G = max_wg;  // the workspace holds max_wg task slots
-  hipLaunchKernelGGL(k_small_loglik, dim3(G), dim3(STHREADS), 0, st, d_tasks, ntask, d_counter, d_ws,
-                     (int64_t)small_workspace_doubles(nmax), d_out);
-  return check_launch("small_loglik");
+  const int64_t stride = (int64_t)small_workspace_doubles(nmax);
+  for (int g = 0; g < ntask; g += slots) {
+    const int cnt = std::min(slots, ntask - g), cnt8 = (cnt + 7) / 8 * 8;
+    const SmallTask *tk = d_tasks + g;
+    int64_t big = 1;
+    for (int i = 0; i < cnt; ++i) big = std::max(big, h_tasks[g + i].n);
+    const int nk = small_blocks(big), per = nk * (nk + 1) / 2;
+    hipLaunchKernelGGL(k_small_prep, dim3(cnt), dim3(256), 0, st, tk, d_ws, stride);
+    hipLaunchKernelGGL(k_small_cov, dim3(cnt8 * per), dim3(256), 0, st, tk, cnt, d_ws, stride, per);
+    if (int rc = check_launch("small_cov")) return rc;
+    for (int t = -1; t < nk; ++t) {
+      const int rows = t < 0 ? 0 : std::max(0, nk - (t + 2));  // rows R >= t + 2
+      const int p = rows ? rows + 2 : 0;
+      hipLaunchKernelGGL(k_small_step, dim3(cnt + cnt8 * p), dim3(256), 0, st, tk, cnt, d_ws, stride,
+                         t, std::max(1, p), d_out + 4 * (int64_t)g);
+      if (int rc = check_launch("small_step")) return rc;
+    }
+  }
+  return 0;
 }
 
 }  // namespace mvg

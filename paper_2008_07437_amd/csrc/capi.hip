@@ -234,6 +234,7 @@ static void release_cached(hipStream_t st) {
 }
 
 hipError_t malloc_async(void **p, size_t bytes, hipStream_t st) {
+  release_stream();  // the pool keeps freed memory mapped from the first call on
   if (hipMallocAsync(p, bytes ? bytes : 8, st) == hipSuccess) return hipSuccess;
   hipGetLastError();
   release_cached(st);
@@ -972,23 +973,26 @@ static int loglik_mixed(const double *d_x, const double *d_y, const double *d_z,
 static int run_small(const std::vector<SmallTask> &tasks, int64_t nmax, double *h_loglik,
                      double *h_logdet, double *h_quad, int64_t *h_status, hipStream_t st) {
   const int nt = (int)tasks.size();
-  const int G = small_batch_workgroups(nt);
-  const size_t wsd = small_workspace_doubles(nmax) * (size_t)G;
+  const size_t tb = (sizeof(SmallTask) * nt + 255) / 256 * 256;
+  const size_t ob = sizeof(double) * 4 * nt, fixed = tb + (ob + 255) / 256 * 256;
+  const size_t slot = sizeof(double) * small_workspace_doubles(nmax);
+  // fewer workspaces (more groups of tasks, the same results) where memory is short
+  int slots = small_batch_slots(nt);
   char *buf = nullptr;
-  const size_t tb = sizeof(SmallTask) * nt, ob = sizeof(double) * 4 * nt;
-  const size_t bytes = tb + ob + sizeof(double) * wsd + 256;
-  if (malloc_async((void **)&buf, bytes, st) != hipSuccess) {
+  while (malloc_async((void **)&buf, fixed + slot * slots, st) != hipSuccess) {
     hipGetLastError();
-    set_error("batched likelihood workspace of %.2f GB failed", bytes / 1e9);
-    return MVG_ERR_ALLOC;
+    if (slots == 1) {
+      set_error("batched likelihood workspace of %.2f GB failed", (fixed + slot) / 1e9);
+      return MVG_ERR_ALLOC;
+    }
+    slots = (slots + 1) / 2;
   }
   SmallTask *d_tasks = (SmallTask *)buf;
-  double *d_out = (double *)(buf + (tb + 255) / 256 * 256);
-  int *d_counter = (int *)(d_out + 4 * nt);
-  double *d_ws = (double *)((char *)d_counter + 256);
-  hipMemcpyAsync(d_tasks, tasks.data(), tb, hipMemcpyHostToDevice, st);
+  double *d_out = (double *)(buf + tb);
+  double *d_ws = (double *)(buf + fixed);
+  hipMemcpyAsync(d_tasks, tasks.data(), sizeof(SmallTask) * nt, hipMemcpyHostToDevice, st);
   int hp = prof_begin(MVG_PROF_POTRF, st, 0.0, 0.0);
-  int rc = launch_small_loglik(d_tasks, nt, nmax, d_counter, d_ws, d_out, st);
+  int rc = launch_small_loglik(d_tasks, tasks.data(), nt, nmax, d_ws, slots, d_out, st);
   prof_end(hp, st);
   std::vector<double> out(4 * nt);
   if (!rc) hipMemcpyAsync(out.data(), d_out, ob, hipMemcpyDeviceToHost, st);

@@ -5,7 +5,7 @@
 // reflection 1, expansion 2, contraction 1/2, shrink 1/2.  The objective is
 // evaluated in batches: the starting simplex (dim + 1 points) and every shrink
 // (dim points) go to the likelihood in one call, which runs them on one
-// matrix, or in one persistent launch when the problem is small.
+// matrix, or in one batch when the problem is small.
 //
 // Host code only (no kernels): the likelihood itself is the GPU path.
 #include <hip/hip_runtime.h>
@@ -167,7 +167,7 @@ static int loglik_objective(int m, const double *V, double *f, void *vctx) {
   mvg_opts d{};
   if (c->o) d = *c->o;
   if (d.precision == MVG_FP64 && 2 * c->n <= MVG_SMALL_MAX_ROWS) {
-    // small problems: every batch size in one persistent launch, so a theta
+    // small problems: every batch size on the batched path, so a theta
     // gets the same value whichever step evaluates it
     std::vector<mvg_task> tk(m);
     for (int i = 0; i < m; ++i) tk[i] = mvg_task{c->x, c->y, c->z, c->n, th[i]};

@@ -207,7 +207,7 @@ int morton_sort(const double *d_x, const double *d_y, int64_t n, int64_t *d_perm
                 double *d_ys, hipStream_t st);
 int launch_trmv(const mvg_mat *L, const double *d_eps, double *d_z, hipStream_t st);
 
-// many small likelihoods in one persistent launch (one workgroup per task)
+// many small likelihoods together, one launch per 64 columns of all of them
 constexpr int SMALL_MAX = 1024;  // 2n bound of a task
 struct SmallTask {
   const double *x, *y, *z;  // device, n locations, 2n values
@@ -215,15 +215,15 @@ struct SmallTask {
   MaternArgs P;
   double t0, t1;            // pivot tolerances (2^-40 sigma_ii^2)
 };
-// out: 4 per task; d_ws holds one small_workspace_doubles(nmax) slot per
-// workgroup, min(small_batch_workgroups(ntask), max_wg if > 0) workgroups
-int launch_small_loglik(const SmallTask *d_tasks, int ntask, int64_t nmax, int *d_counter,
-                        double *d_ws, double *d_out, hipStream_t st, int max_wg = 0);
+// out: 4 per task; d_ws holds `slots` workspaces of small_workspace_doubles(nmax),
+// at most that many tasks advance together.  d_tasks: the device copy of h_tasks
+int launch_small_loglik(const SmallTask *d_tasks, const SmallTask *h_tasks, int ntask, int64_t nmax,
+                        double *d_ws, int slots, double *d_out, hipStream_t st);
 // a task of the batched kernel from a dataset and theta (theta validated by the caller)
 SmallTask small_task(const double *x, const double *y, const double *z, int64_t n,
                      const mvg_theta &th);
 size_t small_workspace_doubles(int64_t nmax);
-int small_batch_workgroups(int ntask);
+int small_batch_slots(int ntask);  // workspaces worth holding for ntask tasks
 
 // second stream of the calling thread for look-ahead (default priority)
 hipStream_t side_stream();

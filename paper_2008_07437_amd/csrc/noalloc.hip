@@ -2,18 +2,18 @@
 // with its scratch memory in a fixed device array instead of an allocation,
 // for callers that cannot allocate device memory.
 //
-// The scratch (task list, per-task outputs, the task-queue counter and one
-// N x N workspace per workgroup of the persistent kernel) lives in `scratch`,
-// a file-scope device array of MVG_NOALLOC_SCRATCH_BYTES.  Each device the
+// The scratch (task list, per-task outputs and one workspace for each task
+// that advances at the same time) lives in `scratch`, a file-scope device array of MVG_NOALLOC_SCRATCH_BYTES.  Each device the
 // library runs on holds its own copy until the process ends.  Host code never
 // passes the array's name to a kernel (that is a host-side stand-in, not a
 // device address): the first call on a device looks up the device address
 // with hipGetSymbolAddress, with that device current, and keeps it per device.
-// The kernels are those of loglik_many; fewer workgroups take the tasks from
-// the same queue when the array holds fewer workspaces than loglik_many
-// would allocate, so every task's result is the one loglik_many gives.
+// The kernels are those of loglik_many; the tasks go in groups when the array
+// holds fewer workspaces than loglik_many would allocate, and every task's
+// result is the one loglik_many gives.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "mvgeo.h"
@@ -84,10 +84,10 @@ int loglik_many_noalloc(const mvg_task *h_tasks, int n_tasks, double *h_loglik, 
     g_tasks[i] = small_task(t.x, t.y, t.z, t.n_loc, t.theta);
     nmax = t.n_loc > nmax ? t.n_loc : nmax;
   }
-  // layout: tasks | outputs (4 per task) | counter | workspaces (one per workgroup)
+  // layout: tasks | outputs (4 per task) | workspaces (one per task that advances)
   const size_t tb = round256(sizeof(SmallTask) * (size_t)n_tasks);
   const size_t ob = round256(sizeof(double) * 4 * (size_t)n_tasks);
-  const size_t fixed = tb + ob + 256;
+  const size_t fixed = tb + ob;
   const size_t slot = sizeof(double) * small_workspace_doubles(nmax);
   if (fixed + slot > (size_t)MVG_NOALLOC_SCRATCH_BYTES) {
     set_error("loglik_many_noalloc: %d tasks of up to %lld locations need %.1f MB, above the "
@@ -100,7 +100,6 @@ int loglik_many_noalloc(const mvg_task *h_tasks, int n_tasks, double *h_loglik, 
   if (int rc = scratch_address(&base)) return rc;
   SmallTask *d_tasks = (SmallTask *)base;
   double *d_out = (double *)(base + tb);
-  int *d_counter = (int *)(base + tb + ob);
   double *d_ws = (double *)(base + fixed);
   hipStream_t st = (hipStream_t)hip_stream;
   if (hipMemcpyAsync(d_tasks, g_tasks, sizeof(SmallTask) * (size_t)n_tasks, hipMemcpyHostToDevice,
@@ -108,8 +107,8 @@ int loglik_many_noalloc(const mvg_task *h_tasks, int n_tasks, double *h_loglik, 
     set_error("loglik_many_noalloc: task upload failed: %s", hipGetErrorString(hipGetLastError()));
     return MVG_ERR_LAUNCH;
   }
-  // the counter is cleared by a kernel inside the launcher (no memset)
-  int rc = launch_small_loglik(d_tasks, n_tasks, nmax, d_counter, d_ws, d_out, st, slots);
+  int rc = launch_small_loglik(d_tasks, g_tasks, n_tasks, nmax, d_ws,
+                               std::min(slots, small_batch_slots(n_tasks)), d_out, st);
   if (!rc && hipMemcpyAsync(g_out, d_out, sizeof(double) * 4 * (size_t)n_tasks,
                             hipMemcpyDeviceToHost, st) != hipSuccess) {
     set_error("loglik_many_noalloc: result copy failed: %s", hipGetErrorString(hipGetLastError()));

@@ -7,7 +7,7 @@
 // request is never overtaken by more than MAX_BYPASS others, so a large
 // request is not starved by a stream of small ones).  Small likelihood
 // requests (2n <= SMALL_MAX, FP64) that are waiting when a worker frees up
-// are taken together and evaluated in one persistent launch.  Workers run on
+// are taken together and evaluated in one batch.  Workers run on
 // their own streams, so admitted requests overlap on the device.
 //
 // Resident factors.  A likelihood request keeps its factor (and Sigma^-1 Z)

@@ -88,3 +88,23 @@ def test_first_failing_pivot(lib, orc, at):
     got = lib.loglik(_dev(x), _dev(y), _dev(z), synthetic.THETA_REF, {"nb": 128})
     assert ref["info"] > 0 and got["status"][0] == ref["info"]
     assert got["loglik"][0] == -np.inf
+
+
+def test_batched_block_edges(lib, orc):
+    """Tasks of one block to sixteen, at the edges of the blocks, in one batch;
+    the no-allocation form (groups of tasks) gives the same bits."""
+    sizes = [1, 2, 31, 32, 33, 63, 64, 65, 96, 97, 255, 256, 257, 480, 511, 512]
+    tasks, ref = [], []
+    for i, n in enumerate(sizes):
+        th = synthetic.jittered_thetas(1, 40 + i)[0]
+        x, y = _sites(orc, n, 50 + i)
+        z = orc.simulate_z(x, y, th, synthetic.normal_eps(2 * n, 50 + i))
+        tasks.append((_dev(x), _dev(y), _dev(z), th))
+        ref.append(orc.loglik(x, y, z, th))
+    got = lib.loglik_many(tasks)
+    for i, r in enumerate(ref):
+        for key in ("loglik", "logdet", "quad"):
+            assert abs(got[key][i] - r[key]) <= 1e-9 * max(abs(r[key]), 1.0), (sizes[i], key)
+    again = lib.loglik_many_noalloc(tasks * 8)
+    for key in ("loglik", "logdet", "quad", "status"):
+        assert np.array_equal(again[key], np.tile(got[key], 8)), key

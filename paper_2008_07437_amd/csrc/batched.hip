@@ -51,12 +51,12 @@ struct SmallSlot {
   __device__ double *v() const { return inv(nk); }
   __device__ double *y() const { return v() + CB * nk; }
   __device__ double *qtab() const { return y() + CB * nk; }
-  __device__ int64_t *info() const { return reinterpret_cast<int64_t *>(qtab() + 4 * QN); }
+  __device__ int64_t *info() const { return reinterpret_cast<int64_t *>(qtab() + QTAB); }
 };
 
 size_t small_workspace_doubles(int64_t nmax) {
   const size_t k = small_blocks(nmax);
-  return (k * (k + 1) / 2 + k) * CB * CB + 2 * CB * k + 4 * QN + 32;
+  return (k * (k + 1) / 2 + k) * CB * CB + 2 * CB * k + QTAB + 32;
 }
 
 int small_batch_slots(int ntask) { return std::min(ntask, SMALL_GROUP); }
@@ -72,27 +72,72 @@ __device__ __forceinline__ bool task_of(int b, int ntask, int per, int &task, in
 }
 
 __global__ __launch_bounds__(256) void k_small_prep(const SmallTask *__restrict__ tasks, double *ws,
-                                                    int64_t stride) {
-  const SmallTask &tk = tasks[blockIdx.x];
-  const SmallSlot s{ws + (int64_t)blockIdx.x * stride, small_blocks(tk.n)};
-  for (int k = threadIdx.x; k < QN; k += 256) quad_entry(k, tk.P, s.qtab());
+                                                    int64_t stride, int groups) {
+  const int task = blockIdx.x / groups, grp = blockIdx.x % groups;
+  const SmallTask &tk = tasks[task];
+  const SmallSlot s{ws + (int64_t)task * stride, small_blocks(tk.n)};
+  if (grp > 0 && !tk.P.table) return;
+  theta_tables(grp, tk.P, s.qtab());
+  if (grp > 0) return;
   const int N = 2 * (int)tk.n;
   for (int i = threadIdx.x; i < CB * s.nk; i += 256) s.v()[i] = i < N ? tk.z[i] : 0.0;
   if (threadIdx.x == 0) *s.info() = INT64_MAX;
 }
 
-// One 64 x 64 block of Sigma (32 x 32 location pairs) per workgroup: bound by
-// the quadrature's FP64 arithmetic, the block is written once.
+// Workgroups of a task in k_small_cov: one per 64 x 64 block where the task's
+// polynomials are used; else (few locations, or closed orders) one per 256
+// pairs l >= r, so that no thread is spent on padding or on the upper half.
+__host__ __device__ inline int small_cov_items(int64_t n, bool table) {
+  const int nk = small_blocks(n);
+  return table ? nk * (nk + 1) / 2 : (int)((n * (n + 1) / 2 + 255) / 256);
+}
+
+// Sigma's 2 x 2 block of the pair (l, r) into its 64 x 64 block.
+__device__ __forceinline__ void small_put(const SmallSlot &s, int l, int r, const double c[3]) {
+  double *B = s.blk(l / 32, r / 32) + (2 * (r % 32)) * CB + 2 * (l % 32);
+  *reinterpret_cast<double2 *>(B) = make_double2(c[0], c[2]);
+  *reinterpret_cast<double2 *>(B + CB) = make_double2(c[2], c[1]);
+}
+
+// Pair q of the n (n + 1) / 2 pairs l >= r: columns r and n - 1 - r together
+// hold n + 1 pairs, one folded row of them.
+template <int FORM>
+__device__ __forceinline__ void small_pairs(const SmallTask &tk, const SmallSlot &s, int item,
+                                            double *ct) {
+  const int n = (int)tk.n, q = item * 256 + threadIdx.x;
+  load_cov_table<FORM>(s.qtab(), ct);
+  if (q < n * (n + 1) / 2) {
+    const int fi = q / (n + 1), fc = q % (n + 1);
+    const bool first = fc < n - fi;
+    const int r = first ? fi : n - 1 - fi, l = first ? fi + fc : r + (fc - (n - fi));
+    double c[3];
+    cross_cov_block<FORM>(tk.x[l], tk.y[l], tk.x[r], tk.y[r], tk.P, ct, s.qtab(), c);
+    small_put(s, l, r, c);
+  }
+  // padding locations n .. 32 nk - 1: unit diagonal, zeros before it
+  const int pad = 32 * s.nk - n, items = small_cov_items(n, false);
+  for (int i = q; i < pad * 32 * s.nk; i += 256 * items) {
+    const int l = n + i / (32 * s.nk), r = i % (32 * s.nk);
+    const double d = l == r ? 1.0 : 0.0, c[3] = {d, d, 0.0};
+    if (r <= l) small_put(s, l, r, c);
+  }
+}
+
 __global__ __launch_bounds__(256) void k_small_cov(const SmallTask *__restrict__ tasks, int ntask,
                                                    double *ws, int64_t stride, int per) {
-  __shared__ double sq[4 * QN];
+  __shared__ double ct[CT_SIZE];
   int task, item;
   if (!task_of(blockIdx.x, ntask, per, task, item)) return;
   const SmallTask &tk = tasks[task];
   const SmallSlot s{ws + (int64_t)task * stride, small_blocks(tk.n)};
-  if (item >= s.nk * (s.nk + 1) / 2) return;
-  for (int i = threadIdx.x; i < 4 * QN; i += 256) sq[i] = s.qtab()[i];
-  __syncthreads();
+  if (item >= small_cov_items(tk.n, tk.P.table)) return;
+  if (!tk.P.table) {
+    if (tk.P.any_quad) small_pairs<COV_QUAD>(tk, s, item, ct);
+    else small_pairs<COV_CLOSED>(tk, s, item, ct);
+    return;
+  }
+  const MaternArgs P = tk.P;
+  load_cov_table<COV_TABLE>(s.qtab(), ct);
   int R = (int)((sqrtf(8.0f * (float)item + 1.0f) - 1.0f) * 0.5f);
   while ((R + 1) * (R + 2) / 2 <= item) ++R;
   while (R * (R + 1) / 2 > item) --R;
@@ -100,7 +145,6 @@ __global__ __launch_bounds__(256) void k_small_cov(const SmallTask *__restrict__
   const int pl = threadIdx.x & 31, gl = 32 * R + pl;
   const double xl = gl < n ? tk.x[gl] : 0.0, yl = gl < n ? tk.y[gl] : 0.0;
   double *B = s.blk(R, C) + 2 * pl;
-  const MaternArgs P = tk.P;
   for (int q = 0; q < 4; ++q) {
     const int pr = (threadIdx.x >> 5) * 4 + q, gr = 32 * C + pr;
     double c[3];
@@ -108,7 +152,7 @@ __global__ __launch_bounds__(256) void k_small_cov(const SmallTask *__restrict__
       c[0] = c[1] = gl == gr ? 1.0 : 0.0;
       c[2] = 0.0;
     } else {
-      cross_cov_block(xl, yl, tk.x[gr], tk.y[gr], P, sq, c);
+      cross_cov_block<COV_TABLE>(xl, yl, tk.x[gr], tk.y[gr], P, ct, s.qtab(), c);
     }
     *reinterpret_cast<double2 *>(B + 2 * pr * CB) = make_double2(c[0], c[2]);
     *reinterpret_cast<double2 *>(B + (2 * pr + 1) * CB) = make_double2(c[2], c[1]);
@@ -253,9 +297,16 @@ int launch_small_loglik(const SmallTask *d_tasks, const SmallTask *h_tasks, int 
     const int cnt = std::min(slots, ntask - g), cnt8 = (cnt + 7) / 8 * 8;
     const SmallTask *tk = d_tasks + g;
     int64_t big = 1;
-    for (int i = 0; i < cnt; ++i) big = std::max(big, h_tasks[g + i].n);
-    const int nk = small_blocks(big), per = nk * (nk + 1) / 2;
-    hipLaunchKernelGGL(k_small_prep, dim3(cnt), dim3(256), 0, st, tk, d_ws, stride);
+    int per = 1, tables = 0;
+    for (int i = 0; i < cnt; ++i) {
+      const SmallTask &t = h_tasks[g + i];
+      big = std::max(big, t.n);
+      per = std::max(per, small_cov_items(t.n, t.P.table));
+      tables |= t.P.table;
+    }
+    const int nk = small_blocks(big), groups = tables ? (CT_HI - CT_LO) / CT_GROUP : 1;
+    hipLaunchKernelGGL(k_small_prep, dim3(cnt * groups), dim3(256), 0, st, tk, d_ws, stride,
+                       groups);
     hipLaunchKernelGGL(k_small_cov, dim3(cnt8 * per), dim3(256), 0, st, tk, cnt, d_ws, stride, per);
     if (int rc = check_launch("small_cov")) return rc;
     for (int t = -1; t < nk; ++t) {

@@ -234,7 +234,15 @@ static void release_cached(hipStream_t st) {
 }
 
 hipError_t malloc_async(void **p, size_t bytes, hipStream_t st) {
-  release_stream();  // the pool keeps freed memory mapped from the first call on
+  // the pool keeps freed memory mapped from the thread's first call on
+  static thread_local uint64_t seen = 0;  // devices whose pool is set up
+  int dev = 0;
+  hipGetDevice(&dev);
+  const uint64_t bit = (uint64_t)1 << (dev & 63);
+  if (!(seen & bit)) {
+    release_stream();
+    seen |= bit;
+  }
   if (hipMallocAsync(p, bytes ? bytes : 8, st) == hipSuccess) return hipSuccess;
   hipGetLastError();
   release_cached(st);
@@ -311,7 +319,7 @@ SmallTask small_task(const double *x, const double *y, const double *z, int64_t 
   t.y = y;
   t.z = z;
   t.n = n;
-  matern_setup(&th, &t.P);
+  matern_setup(&th, &t.P, n);
   t.t0 = 0x1p-40 * th.sigma11_sq;
   t.t1 = 0x1p-40 * th.sigma22_sq;
   return t;
@@ -437,7 +445,7 @@ static int mat_alloc(int64_t n_loc, int p, const mvg_opts &o, const double *d_x,
 static int mat_create(int64_t n_loc, const mvg_opts &o, const mvg_theta *th, const double *d_x,
                       const double *d_y, hipStream_t st, mvg_mat **out) {
   MaternArgs margs;
-  if (int rc = matern_setup(th, &margs)) return rc;
+  if (int rc = matern_setup(th, &margs, n_loc)) return rc;
   mvg_mat *A = nullptr;
   if (int rc = mat_alloc(n_loc, 2, o, d_x, d_y, st, &A)) return rc;
   A->theta = *th;
@@ -491,7 +499,7 @@ static int mat_alloc(int64_t n_loc, int p, const mvg_opts &o, const double *d_x,
   ok = ok && (A->d_kind = (int *)dev_alloc(sizeof(int) * nt)) != nullptr;
   ok = ok && (A->d_x = (double *)dev_alloc(sizeof(double) * n_loc)) != nullptr;
   ok = ok && (A->d_y = (double *)dev_alloc(sizeof(double) * n_loc)) != nullptr;
-  ok = ok && (A->d_qtab = (double *)dev_alloc(sizeof(double) * (1 + PORD) * QN)) != nullptr;
+  ok = ok && (A->d_qtab = (double *)dev_alloc(sizeof(double) * std::max(QTAB, (1 + PORD) * QN))) != nullptr;
   ok = ok && (A->d_winv = (double *)dev_alloc(sizeof(double) * (size_t)A->Np * A->nb)) != nullptr;
   if (!ok) {
     hipGetLastError();
@@ -529,14 +537,14 @@ static int tlr_mat_create(int64_t n_loc, const mvg_opts &o, const mvg_theta *th,
   A->precision = MVG_TLR;
   A->theta = *th;
   A->opts = o;
-  if (int rc = matern_setup(th, &A->margs)) {
+  if (int rc = matern_setup(th, &A->margs, n_loc)) {
     delete A;
     return rc;
   }
   A->tlr = new TlrState();
   bool ok = (A->d_x = (double *)dev_alloc(sizeof(double) * n_loc)) != nullptr;
   ok = ok && (A->d_y = (double *)dev_alloc(sizeof(double) * n_loc)) != nullptr;
-  ok = ok && (A->d_qtab = (double *)dev_alloc(sizeof(double) * 4 * QN)) != nullptr;
+  ok = ok && (A->d_qtab = (double *)dev_alloc(sizeof(double) * QTAB)) != nullptr;
   if (!ok) {
     hipGetLastError();
     set_error("device allocation for a %lld-location TLR matrix failed", (long long)n_loc);
@@ -621,12 +629,12 @@ size_t mvg_footprint(int64_t n_loc, const mvg_opts *o) {
     size_t b = sizeof(double) * (3 * (size_t)T * nbp * nbp + (size_t)T * d.nb * d.nb);
     b += sizeof(double) * 2 * nt * 2 * (size_t)d.nb * 64;
     b += sizeof(double) * (size_t)(T + 1) * d.nb * ((size_t)T / 2 * 64 + d.nb);
-    b += sizeof(double) * (size_t)(2 * n_loc + 3 * Np + 4 * QN);
+    b += sizeof(double) * (size_t)(2 * n_loc + 3 * Np + QTAB);
     return b;
   }
   size_t b = layout_bytes(n_loc, d);
   // matrix + inverse diagonal tiles + panel workspace + vectors
-  b += sizeof(double) * (size_t)(2 * n_loc + 3 * Np + 4 * QN + 2 * Np * d.nb);
+  b += sizeof(double) * (size_t)(2 * n_loc + 3 * Np + QTAB + 2 * Np * d.nb);
   b += (sizeof(int64_t) + sizeof(int)) * (size_t)T * (T + 1) / 2;
   if (is_mixed(d.precision)) {
     mvg_opts f = d;
@@ -874,7 +882,7 @@ static int loglik_mixed(const double *d_x, const double *d_y, const double *d_z,
   for (int i = 0; i < n_theta && !rc; ++i) {
     if (i > 0) {
       S->theta = A->theta = th[i];
-      matern_setup(&th[i], &S->margs);
+      matern_setup(&th[i], &S->margs, n_loc);
       A->margs = S->margs;
     }
     int hg = prof_begin(MVG_PROF_GEN, st, 0.0, 8.0 * (double)S->N * (S->N + 1) / 2);
@@ -1228,7 +1236,7 @@ int loglik(const double *d_x, const double *d_y, const double *d_z, int64_t n_lo
   for (int i = 0; i < n_theta && !rc; ++i) {
     if (i > 0) {
       A->theta = th[i];
-      matern_setup(&th[i], &A->margs);
+      matern_setup(&th[i], &A->margs, n_loc);
     }
     const double npair = (double)n_loc * (n_loc + 1) / 2;
     int hg = prof_begin(MVG_PROF_GEN, st, 0.0, 8.0 * (double)A->N * (A->N + 1) / 2);
@@ -1606,7 +1614,8 @@ int cokrige_predict(const mvg_factor *F, const double *d_x0, const double *d_y0,
   if (!d_zhat) return -5;
   hipStream_t st = (hipStream_t)hip_stream;
   const mvg_mat *A = F->A;
-  const int nchunk = (int)((A->n_loc + 2047) / 2048);
+  const int span = cokrige_chunk(A->n_loc, m);
+  const int nchunk = (int)((A->n_loc + span - 1) / span);
   int hc = prof_begin(MVG_PROF_COKRIGE, st, 0.0, 8.0 * (double)A->N);
   double *part = nullptr;
   if (malloc_async((void **)&part, sizeof(double) * 2 * m * nchunk, st) != hipSuccess) {

@@ -17,7 +17,30 @@
 
 namespace mvg {
 
-int matern_setup(const mvg_theta *th, MaternArgs *P) {
+// 1 / Gamma(nu), nu > 0: Taylor series of 1 / Gamma(1 + z) at |z| <= 1/2 (24
+// terms, 2e-16; generated with mpmath) and the recurrence.
+static double rgamma(double nu) {
+  static const double c[] = {
+    1, 0.57721566490153287, -0.6558780715202539,
+    -0.042002635034095237, 0.16653861138229148, -0.042197734555544333,
+    -0.009621971527876973, 0.0072189432466630999, -0.0011651675918590652,
+    -0.00021524167411495098, 0.0001280502823881162, -2.0134854780788239e-05,
+    -1.2504934821426706e-06, 1.1330272319816959e-06, -2.0563384169776071e-07,
+    6.1160951044814161e-09, 5.0020076444692229e-09, -1.18127457048702e-09,
+    1.0434267116911005e-10, 7.7822634399050708e-12, -3.696805618642206e-12,
+    5.1003702874544758e-13, -2.0583260535665066e-14, -5.3481225394230178e-15,
+    1.2267786282382608e-15,
+  };
+  const int n = (int)std::floor(nu + 0.5);
+  const double z = nu - n;
+  double s = 0.0;
+  for (int k = (int)(sizeof(c) / sizeof(c[0])) - 1; k >= 0; --k) s = std::fma(s, z, c[k]);
+  if (n == 0) return s * z;
+  for (int k = 1; k < n; ++k) s /= k + z;
+  return s;
+}
+
+int matern_setup(const mvg_theta *th, MaternArgs *P, int64_t n_loc) {
   if (!th) return -1;
   const double v[6] = {th->sigma11_sq, th->sigma22_sq, th->a, th->nu11, th->nu22, th->beta};
   for (int i = 0; i < 5; ++i)
@@ -38,41 +61,38 @@ int matern_setup(const mvg_theta *th, MaternArgs *P) {
   for (int o = 0; o < 3; ++o) {
     const double nu = P->nu[o];
     P->lnorm[o] = -((nu - 1.0) * std::log(2.0) + std::lgamma(nu));
+    P->norm[o] = std::exp2(1.0 - nu) * rgamma(nu);
     P->closed[o] = nu == 0.5 ? 1 : nu == 1.5 ? 2 : nu == 2.5 ? 3 : 0;
     if (!P->closed[o]) P->any_quad = 1;
   }
+  P->table = P->any_quad && n_loc >= TABLE_MIN_LOC;
   return 0;
 }
 
-__global__ void k_quad_table(MaternArgs P, double *__restrict__ q) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < QN) quad_entry(k, P, q);
+__global__ __launch_bounds__(256) void k_theta_tables(MaternArgs P, double *__restrict__ q) {
+  theta_tables(blockIdx.x, P, q);
 }
 
 int launch_quad_table(const MaternArgs &P, double *d_qtab, hipStream_t st) {
-  hipLaunchKernelGGL(k_quad_table, dim3((QN + 255) / 256), dim3(256), 0, st, P, d_qtab);
-  return check_launch("quad_table");
-}
-
-
-__device__ __forceinline__ void load_qtab(const double *__restrict__ q, double *sq) {
-  for (int i = threadIdx.x; i < 4 * QN; i += blockDim.x) sq[i] = q[i];
-  __syncthreads();
+  hipLaunchKernelGGL(k_theta_tables, dim3(P.table ? (CT_HI - CT_LO) / CT_GROUP : 1), dim3(256), 0,
+                     st, P, d_qtab);
+  return check_launch("theta_tables");
 }
 
 // One workgroup: a 32 x 32 block of location pairs of one lower tile.
 // Thread layout: 32 consecutive pair-rows (coalesced column writes) x 8 groups
 // of 4 pair-columns.
+template <int FORM>
 __global__ __launch_bounds__(256) void k_cov_tiles(MaternArgs P, const double *__restrict__ qtab,
                                                    const double *__restrict__ xs,
                                                    const double *__restrict__ ys, int64_t n_loc,
                                                    TileMap M, int tile_first, int spt) {
-  __shared__ double sq[4 * QN];
+  __shared__ double ct[cov_lds(FORM)];
   const int nsub = spt * spt;
   const int64_t tile = tile_first + blockIdx.x / nsub;
   const int sub = blockIdx.x % nsub;
   if (M.kind && M.kind[tile] == TK_ZERO) return;  // annihilated DST tile (whole workgroup)
-  load_qtab(qtab, sq);
+  load_cov_table<FORM>(qtab, ct);
   int J = 0;
   int64_t t = tile;
   while (t >= M.T - J) {
@@ -100,7 +120,7 @@ __global__ __launch_bounds__(256) void k_cov_tiles(MaternArgs P, const double *_
       c[1] = d;
       c[2] = 0.0;
     } else {
-      cross_cov_block(xl, yl, xs[gr], ys[gr], P, sq, c);
+      cross_cov_block<FORM>(xl, yl, xs[gr], ys[gr], P, ct, qtab, c);
     }
     const int64_t e0 = (int64_t)(2 * pr) * nb + 2 * pl;  // (row 2pl, col 2pr)
     if (kind == TK_F64) {
@@ -125,8 +145,16 @@ int launch_cov_tiles(const MaternArgs &P, const double *d_qtab, const double *d_
   const int64_t per = ((int64_t)1 << 30) / (spt * spt);
   for (int64_t t0 = 0; t0 < tile_count; t0 += per) {
     const int64_t cnt = tile_count - t0 < per ? tile_count - t0 : per;
-    hipLaunchKernelGGL(k_cov_tiles, dim3((unsigned)(cnt * spt * spt)), dim3(256), 0, st, P,
-                       d_qtab, d_x, d_y, n_loc, M, (int)(tile_first + t0), spt);
+    const dim3 grid((unsigned)(cnt * spt * spt));
+#define MVG_FORM(F)                                                                             \
+  hipLaunchKernelGGL(k_cov_tiles<F>, grid, dim3(256), 0, st, P, d_qtab, d_x, d_y, n_loc, M,     \
+                     (int)(tile_first + t0), spt)
+    switch (cov_form(P)) {
+      case COV_TABLE: MVG_FORM(COV_TABLE); break;
+      case COV_QUAD: MVG_FORM(COV_QUAD); break;
+      default: MVG_FORM(COV_CLOSED); break;
+    }
+#undef MVG_FORM
     int rc = check_launch("cov_tiles");
     if (rc) return rc;
   }
@@ -306,30 +334,38 @@ int launch_cov_tiles_p(const MaternArgsP &P, const double *d_qtab, const double 
 
 // ---------------------------------------------------------------- cokriging
 
-constexpr int CK_CHUNK = 2048;  // locations per workgroup
+// Locations per workgroup: up to 2048, fewer where that leaves less than about
+// 1024 workgroups (100 targets on 5,000 locations: 512 a workgroup instead of
+// 2048, one target's sum was the length of the launch).
+int cokrige_chunk(int64_t n_loc, int64_t m) {
+  const int64_t c = (n_loc * m / 1024 + 255) / 256 * 256;
+  return (int)std::min<int64_t>(2048, std::max<int64_t>(256, c));
+}
 
 // part[(t * nchunk + chunk) * 2 + j] = sum over the chunk's locations r and
 // i in {0,1} of C_ij(||s0_t - s_r||) w[2r+i].
+template <int FORM>
 __global__ __launch_bounds__(256) void k_cokrige_dot(MaternArgs P, const double *__restrict__ qtab,
                                                      const double *__restrict__ xs,
                                                      const double *__restrict__ ys, int64_t n_loc,
                                                      const double *__restrict__ x0,
                                                      const double *__restrict__ y0,
                                                      const double *__restrict__ w,
-                                                     double *__restrict__ part, int nchunk) {
-  __shared__ double sq[4 * QN];
+                                                     double *__restrict__ part, int nchunk,
+                                                     int span) {
+  __shared__ double ct[cov_lds(FORM)];
   __shared__ double red[2][256];
-  load_qtab(qtab, sq);
+  load_cov_table<FORM>(qtab, ct);
   const int64_t t = blockIdx.x / nchunk;
   const int chunk = blockIdx.x % nchunk;
   const double xt = x0[t], yt = y0[t];
   double a0 = 0.0, a1 = 0.0;
-  const int64_t r0 = (int64_t)chunk * CK_CHUNK;
-  for (int q = threadIdx.x; q < CK_CHUNK; q += 256) {
+  const int64_t r0 = (int64_t)chunk * span;
+  for (int q = threadIdx.x; q < span; q += 256) {
     const int64_t r = r0 + q;
     if (r >= n_loc) break;
     double c[3];
-    cross_cov_block(xt, yt, xs[r], ys[r], P, sq, c);
+    cross_cov_block<FORM>(xt, yt, xs[r], ys[r], P, ct, qtab, c);
     const double w0 = w[2 * r], w1 = w[2 * r + 1];
     a0 += c[0] * w0 + c[2] * w1;  // Zhat_1 += C11 w_1 + C21 w_2
     a1 += c[2] * w0 + c[1] * w1;  // Zhat_2 += C12 w_1 + C22 w_2
@@ -353,26 +389,36 @@ __global__ __launch_bounds__(256) void k_cokrige_dot(MaternArgs P, const double 
 int launch_cokrige_dot(const MaternArgs &P, const double *d_qtab, const double *d_x,
                        const double *d_y, int64_t n_loc, const double *d_x0, const double *d_y0,
                        int64_t m, const double *d_w, double *d_part, int nchunk, hipStream_t st) {
-  hipLaunchKernelGGL(k_cokrige_dot, dim3((unsigned)(m * nchunk)), dim3(256), 0, st, P, d_qtab,
-                     d_x, d_y, n_loc, d_x0, d_y0, d_w, d_part, nchunk);
+  const dim3 grid((unsigned)(m * nchunk));
+  const int span = cokrige_chunk(n_loc, m);
+#define MVG_FORM(F)                                                                              \
+  hipLaunchKernelGGL(k_cokrige_dot<F>, grid, dim3(256), 0, st, P, d_qtab, d_x, d_y, n_loc, d_x0, \
+                     d_y0, d_w, d_part, nchunk, span)
+  switch (cov_form(P)) {
+    case COV_TABLE: MVG_FORM(COV_TABLE); break;
+    case COV_QUAD: MVG_FORM(COV_QUAD); break;
+    default: MVG_FORM(COV_CLOSED); break;
+  }
+#undef MVG_FORM
   return check_launch("cokrige_dot");
 }
 
 // c0 columns for the MSE: V[(2t + j) * Np + 2r + i] = C_ij(||s0_t - s_r||),
 // padded rows 0.
+template <int FORM>
 __global__ __launch_bounds__(256) void k_cokrige_c0(MaternArgs P, const double *__restrict__ qtab,
                                                     const double *__restrict__ xs,
                                                     const double *__restrict__ ys, int64_t n_loc,
                                                     int64_t Np, const double *__restrict__ x0,
                                                     const double *__restrict__ y0,
                                                     double *__restrict__ V) {
-  __shared__ double sq[4 * QN];
-  load_qtab(qtab, sq);
+  __shared__ double ct[cov_lds(FORM)];
+  load_cov_table<FORM>(qtab, ct);
   const int64_t t = blockIdx.y;
   const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (2 * r >= Np) return;
   double c[3] = {0.0, 0.0, 0.0};
-  if (r < n_loc) cross_cov_block(x0[t], y0[t], xs[r], ys[r], P, sq, c);
+  if (r < n_loc) cross_cov_block<FORM>(x0[t], y0[t], xs[r], ys[r], P, ct, qtab, c);
   double *v0 = V + (2 * t) * Np, *v1 = V + (2 * t + 1) * Np;
   v0[2 * r] = c[0];
   v0[2 * r + 1] = c[2];
@@ -384,8 +430,16 @@ int launch_cokrige_c0(const MaternArgs &P, const double *d_qtab, const double *d
                       const double *d_y, int64_t n_loc, int64_t Np, const double *d_x0,
                       const double *d_y0, int64_t m, double *d_c0, hipStream_t st) {
   const int64_t npair = Np / 2;
-  hipLaunchKernelGGL(k_cokrige_c0, dim3((unsigned)((npair + 255) / 256), (unsigned)m), dim3(256),
-                     0, st, P, d_qtab, d_x, d_y, n_loc, Np, d_x0, d_y0, d_c0);
+  const dim3 grid((unsigned)((npair + 255) / 256), (unsigned)m);
+#define MVG_FORM(F)                                                                             \
+  hipLaunchKernelGGL(k_cokrige_c0<F>, grid, dim3(256), 0, st, P, d_qtab, d_x, d_y, n_loc, Np,   \
+                     d_x0, d_y0, d_c0)
+  switch (cov_form(P)) {
+    case COV_TABLE: MVG_FORM(COV_TABLE); break;
+    case COV_QUAD: MVG_FORM(COV_QUAD); break;
+    default: MVG_FORM(COV_CLOSED); break;
+  }
+#undef MVG_FORM
   return check_launch("cokrige_c0");
 }
 

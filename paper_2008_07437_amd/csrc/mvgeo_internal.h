@@ -36,18 +36,41 @@ __host__ __device__ constexpr double qlev_xmax(int j) {
   return j == 0 ? 6.0 : j == 1 ? 24.0 : j == 2 ? 96.0 : j == 3 ? 384.0 : 1536.0;
 }
 
+// Piecewise polynomials of g_o(x) = e^x M(x; nu_o), o = (1,1), (2,2), (1,2):
+// each octave [2^e, 2^(e+1)), CT_LO <= e < CT_HI, in CT_SUB equal parts, degree
+// CT_DEG in z in [-1, 1], fitted at the Chebyshev nodes from the quadrature.
+// g's nearest singularity is x = 0, at least 9 half-widths from a part's
+// centre, so the interpolation error is below (9 + sqrt 80)^-13 = 5e-17.
+constexpr int CT_LO = -14, CT_HI = 10, CT_SUB = 4, CT_DEG = 12;
+constexpr int CT_NODES = CT_DEG + 1;
+constexpr int CT_ROW = 3 * CT_NODES;  // a part's coefficients, [power][order]
+constexpr int CT_SIZE = (CT_HI - CT_LO) * CT_SUB * CT_ROW;
+constexpr int CT_GROUP = 4;  // octaves formed by one workgroup
+static_assert((CT_HI - CT_LO) % CT_GROUP == 0, "whole groups of octaves");
+constexpr int QTAB = 4 * QN + CT_SIZE;  // a theta's tables: quadrature, polynomials
+
 // Per-theta constants of Eq. (2) for the orders o = 0 (1,1), 1 (2,2), 2 (1,2).
 struct MaternArgs {
   double a;
   double coef[3];   // sigma11^2, sigma22^2, rho12 sigma1 sigma2
   double nu[3];     // nu11, nu22, nu12
   double lnorm[3];  // -log(2^(nu-1) Gamma(nu))
+  double norm[3];   // 1 / (2^(nu-1) Gamma(nu))
   int closed[3];    // 0: quadrature; 1: nu = 1/2; 2: nu = 3/2; 3: nu = 5/2
   int any_quad;
+  int table;        // covariances from the polynomials (else the quadrature at every pair)
 };
 
-// Validates theta and fills the constants; returns 0 or -(index of the bad entry).
-int matern_setup(const mvg_theta *th, MaternArgs *out);
+// From this many locations on a theta's polynomials are worth forming.  Their
+// 1,248 nodes cost 20 us, or 0.18 us a theta in a large batch, a pair from
+// them a sixth of a quadrature: 1024 theta take 181 us of tables against 188
+// of quadrature at n = 128 (47 at n = 64); one theta at n = 200 31 us for
+// tables and covariances against 37.
+constexpr int64_t TABLE_MIN_LOC = 128;
+
+// Validates theta and fills the constants; returns 0 or -(index of the bad
+// entry).  n_loc: locations of the matrix that it is for.
+int matern_setup(const mvg_theta *th, MaternArgs *out, int64_t n_loc = 0);
 
 // The p-variate model: orders o(i, j), i <= j, packed row by row
 // (o = i p - i (i - 1) / 2 + j - i); the quadrature table holds
@@ -143,6 +166,7 @@ int launch_cov_tiles(const MaternArgs &P, const double *d_qtab, const double *d_
 // p-variate Sigma (p != 2 or on request) over all tiles of M
 int launch_cov_tiles_p(const MaternArgsP &P, const double *d_qtab, const double *d_x,
                        const double *d_y, int64_t n_loc, TileMap M, hipStream_t st);
+int cokrige_chunk(int64_t n_loc, int64_t m);  // locations per partial sum of cokrige_dot
 // c0^T w and optionally ||L^-1 c0||^2 pieces for cokriging
 int launch_cokrige_dot(const MaternArgs &P, const double *d_qtab, const double *d_x,
                        const double *d_y, int64_t n_loc, const double *d_x0, const double *d_y0,

@@ -1,0 +1,33 @@
+"""Generated covariances at the edges of the tables they are evaluated from:
+the octaves and their quarters, below the first and above the last octave,
+against the oracle's own K_nu.  Tolerance: 2e-13 relative (both sides evaluate
+K_nu to a few 1e-15 with different methods; the factor e^-x carries x times
+the rounding of x, 1e-13 at x = 600)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nu", [(0.5, 1.0), (0.3, 0.9), (1.5, 0.7), (2.5, 4.9)])
+@pytest.mark.parametrize("a", [1.0, 0.37])
+def test_table_edges(orc, nu, a):
+    import torch
+    import paper_2008_07437_amd as mvg
+    th = (1.3, 0.8, a, nu[0], nu[1], 0.4)
+    print("table edges nu=%s a=%g" % (nu, a), flush=True)
+    edge = np.array([2.0 ** e * (1 + s / 4) for e in range(-16, 10) for s in range(4)])
+    x = np.concatenate([edge, np.nextafter(edge, 0), np.nextafter(edge, 1e9), edge * 1.1,
+                        [1e-9, 1e-6, 1023.0, 1024.0, 1025.0, 1535.0, 1537.0, 5000.0]])
+    h = np.unique(x * a)
+    xs = np.concatenate([[0.0], h])
+    d = torch.as_tensor(xs).cuda()
+    A = mvg.cov_generate(d, torch.zeros_like(d), th, {"nb": 128})
+    k = np.arange(1, h.size + 1)
+    r = np.concatenate([2 * k, 2 * k + 1, 2 * k + 1, 2 * k])
+    c = np.concatenate([0 * k, 0 * k + 1, 0 * k, 0 * k + 1])
+    got = A.gather(r, c).cpu().numpy()
+    ref = orc.cov_entries(xs, np.zeros_like(xs), th, r, c)
+    big = np.abs(ref) > 1e-280
+    assert np.max(np.abs(got[big] - ref[big]) / np.abs(ref[big])) <= 2e-13
+    assert np.all(np.abs(got[~big]) <= 1e-280)

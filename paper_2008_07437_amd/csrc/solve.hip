@@ -19,117 +19,161 @@ constexpr int VB = 64;  // rows per workgroup chunk of the per-column kernels
 // The diagonal tiles are solved with the inverses W_k kept by the
 // factorisation: each step is a dense triangular matrix-vector product.
 
-// y_k = W_k x_k (W_k lower triangular, column-major): 64 output rows per
-// workgroup (nb / 64 workgroups per right-hand side), the four waves take a
-// quarter of the columns c <= r each and are added in a fixed order.  Reads
-// x from X, writes y to Y (out of place: other workgroups still read x).
+// One step is two launches on the serial chain (the tile's W_k, then its
+// column), so each is cut for latency: 32 output rows (or 16 output columns
+// of a transposed product) per workgroup, two rows a load, eight or more loads
+// of a lane in flight, sums in a fixed order.  Before (64 rows a workgroup, a
+// quarter of the columns per wave two at a time): 36 us for the tile and 19
+// for the column at nb = 512 and 6 tiles, now 5 and 5; at nb = 1024 and 49 tiles
+// 112 and 74 forward, 115 and 133 backward, now 9 and 40, 6 and 38 (5 TB/s over
+// the column's bytes).
+constexpr int SR = 32;  // output rows of a forward workgroup
+constexpr int SC = 16;  // output columns of a transposed one
+constexpr int SU = 8;   // loads of a lane in flight
+
+template <class T>
+struct Pair;
+template <>
+struct Pair<double> {
+  typedef double2 type;
+};
+template <>
+struct Pair<float> {
+  typedef float2 type;
+};
+
+// sum over columns c < nc of A[r][c] x[c] for the 32 rows at A (column-major,
+// ld nb); x in LDS, nc a multiple of 16.  Thread (pair p of rows, group g)
+// takes columns g, g + 16, ...; the groups are added in order by the threads
+// below 32, which get their row's sum.
+template <class T>
+__device__ __forceinline__ double rows_dot(const T *A, int nb, int nc, const double *x,
+                                           double (*part)[SR]) {
+  const int p = threadIdx.x & 15, g = threadIdx.x >> 4;
+  const int n = nc / 16;
+  double s0 = 0.0, s1 = 0.0;
+  for (int i = 0; i < n; i += SU) {
+    typename Pair<T>::type v[SU];
+#pragma unroll
+    for (int u = 0; u < SU; ++u)
+      v[u] = *reinterpret_cast<const typename Pair<T>::type *>(
+          A + (int64_t)(g + 16 * min(i + u, n - 1)) * nb + 2 * p);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < SU; ++u) {
+      const double xc = i + u < n ? x[g + 16 * min(i + u, n - 1)] : 0.0;
+      s0 = fma((double)v[u].x, xc, s0);
+      s1 = fma((double)v[u].y, xc, s1);
+    }
+  }
+  part[g][2 * p] = s0;
+  part[g][2 * p + 1] = s1;
+  __syncthreads();
+  double s = 0.0;
+  if (threadIdx.x < SR)
+#pragma unroll
+    for (int q = 0; q < 16; ++q) s += part[q][threadIdx.x];
+  return s;
+}
+
+// sum over rows r < nr of A[r][c] x[r] for the 16 columns at A (column-major,
+// ld nb); x in LDS, nr even.  A wave takes four columns, its lanes row pairs;
+// every lane gets the four sums.
+template <class T>
+__device__ __forceinline__ void cols_dot(const T *A, int nb, int nr, const double *x, double s[4]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const T *a = A + (int64_t)(4 * w) * nb;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) s[c] = 0.0;
+  for (int r0 = 0; r0 < nr; r0 += 256) {
+    typename Pair<T>::type v[2][4];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        v[u][c] = *reinterpret_cast<const typename Pair<T>::type *>(
+            a + (int64_t)c * nb + min(r0 + 128 * u + 2 * lane, nr - 2));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int r = r0 + 128 * u + 2 * lane;
+      const double x0 = r < nr ? x[min(r, nr - 2)] : 0.0, x1 = r < nr ? x[min(r, nr - 2) + 1] : 0.0;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        s[c] = fma((double)v[u][c].y, x1, fma((double)v[u][c].x, x0, s[c]));
+    }
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) s[c] += __shfl_xor(s[c], o);
+}
+
+// y_k = W_k x_k (W_k lower triangular with its zeros stored, column-major):
+// 32 output rows per workgroup.  Reads x from X, writes y to Y (out of place:
+// other workgroups still read x).
 __global__ __launch_bounds__(256) void k_trsv_tile_fwd(int nb, int k, const double *__restrict__ winv,
                                                        const double *__restrict__ X,
                                                        double *__restrict__ Y, int64_t ldv) {
-  __shared__ double v[1024];
-  __shared__ double part[4][64];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r0 = blockIdx.x * 64, r = r0 + lane;
-  const double *xk = X + (int64_t)blockIdx.z * ldv + (int64_t)k * nb;
-  const double *W = winv + (int64_t)k * nb * nb;
-  const int cend = r0 + 64;  // columns c < cend can meet rows r0..r0+63
-  for (int c = tid; c < cend; c += 256) v[c] = xk[c];
+  __shared__ double v[1024], part[16][SR];
+  const int r0 = blockIdx.x * SR;
+  const int64_t off = (int64_t)blockIdx.z * ldv + (int64_t)k * nb;
+  const int nc = r0 + SR;  // columns that meet rows r0 .. r0 + 31
+  for (int c = threadIdx.x; c < nc; c += 256) v[c] = X[off + c];
   __syncthreads();
-  const int q = cend / 4;    // a multiple of 16
-  double s0 = 0.0, s1 = 0.0;
-  for (int c = wave * q; c < wave * q + q; c += 2) {
-    if (c <= r) s0 += W[(int64_t)c * nb + r] * v[c];
-    if (c + 1 <= r) s1 += W[(int64_t)(c + 1) * nb + r] * v[c + 1];
-  }
-  part[wave][lane] = s0 + s1;
-  __syncthreads();
-  if (tid < 64)
-    Y[(int64_t)blockIdx.z * ldv + (int64_t)k * nb + r0 + tid] =
-        (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
+  const double s = rows_dot(winv + (int64_t)k * nb * nb + r0, nb, nc, v, part);
+  if (threadIdx.x < SR) Y[off + r0 + threadIdx.x] = s;
 }
 
-// v_i -= L_ik y_k for tiles i in (k, T), y_k read from Y: 64 rows per
-// workgroup, the four waves take a quarter of the columns each and are added
-// in a fixed order.
+// v_i -= L_ik y_k for tiles i in (k, T), y_k read from Y: 32 rows per
+// workgroup.
 __global__ __launch_bounds__(256) void k_gemv_fwd(TileMap M, int k, double *__restrict__ V,
                                                  const double *__restrict__ Y, int64_t ldv) {
-  __shared__ double y[1024];
-  __shared__ double part[4][64];
-  const int nb = M.nb, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  double *Vc = V + (int64_t)blockIdx.z * ldv;
-  const int chunks = nb / 64;
-  const int i = k + 1 + blockIdx.x / chunks;
-  const int r = (blockIdx.x % chunks) * 64 + lane;
-  for (int c = tid; c < nb; c += 256) y[c] = Y[(int64_t)blockIdx.z * ldv + (int64_t)k * nb + c];
+  __shared__ double y[1024], part[16][SR];
+  const int nb = M.nb, chunks = nb / SR;
+  const int i = k + 1 + blockIdx.x / chunks, r0 = (blockIdx.x % chunks) * SR;
+  const int64_t off = (int64_t)blockIdx.z * ldv;
+  for (int c = threadIdx.x; c < nb; c += 256) y[c] = Y[off + (int64_t)k * nb + c];
   __syncthreads();
-  const int q = nb / 4;
-  double s0 = 0.0, s1 = 0.0;
-  if (tile_is_f32(M, i, k)) {  // mixed precision: off-band tiles in FP32
-    const float *L = tile_ptr_f32(M, i, k) + r;
-    for (int c = wave * q; c < wave * q + q; c += 2) {
-      s0 += (double)L[(int64_t)c * nb] * y[c];
-      s1 += (double)L[(int64_t)(c + 1) * nb] * y[c + 1];
-    }
-  } else {
-    const double *L = tile_ptr(M, i, k) + r;
-    for (int c = wave * q; c < wave * q + q; c += 2) {
-      s0 += L[(int64_t)c * nb] * y[c];
-      s1 += L[(int64_t)(c + 1) * nb] * y[c + 1];
-    }
-  }
-  part[wave][lane] = s0 + s1;
-  __syncthreads();
-  if (tid < 64)
-    Vc[(int64_t)i * nb + r] -= (part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid]);
+  const double s = tile_is_f32(M, i, k)  // mixed precision: off-band tiles in FP32
+                       ? rows_dot(tile_ptr_f32(M, i, k) + r0, nb, nb, y, part)
+                       : rows_dot(tile_ptr(M, i, k) + r0, nb, nb, y, part);
+  if (threadIdx.x < SR) V[off + (int64_t)i * nb + r0 + threadIdx.x] -= s;
 }
 
-// y_k = W_k^T x_k: output c = sum_{r >= c} W[r][c] x[r] (column c of W_k is
-// contiguous); 64 outputs per workgroup (nb / 64 workgroups per right-hand
-// side), one wave per output at a time, lanes over rows.  Out of place.
+// y_k = W_k^T x_k: 16 outputs per workgroup, rows from the outputs' own 64-row
+// block on (zeros above the diagonal are stored).  Out of place.
 __global__ __launch_bounds__(256) void k_trsv_tile_bwd(int nb, int k, const double *__restrict__ winv,
                                                        const double *__restrict__ X,
                                                        double *__restrict__ Y, int64_t ldv) {
   __shared__ double v[1024];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c0 = blockIdx.x * 64;
-  const double *xk = X + (int64_t)blockIdx.z * ldv + (int64_t)k * nb;
-  const double *W = winv + (int64_t)k * nb * nb;
-  for (int r = c0 + tid; r < nb; r += 256) v[r] = xk[r];
+  const int c0 = blockIdx.x * SC, rb = c0 / 64 * 64;
+  const int64_t off = (int64_t)blockIdx.z * ldv + (int64_t)k * nb;
+  for (int r = threadIdx.x; r < nb - rb; r += 256) v[r] = X[off + rb + r];
   __syncthreads();
-  for (int c = c0 + wave; c < c0 + 64; c += 4) {
-    const double *col = W + (int64_t)c * nb;
-    double t = 0.0;
-    for (int r = c + lane; r < nb; r += 64) t += col[r] * v[r];
-    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
-    if (lane == 0) Y[(int64_t)blockIdx.z * ldv + (int64_t)k * nb + c] = t;
-  }
+  double s[4];
+  cols_dot(winv + (int64_t)k * nb * nb + (int64_t)c0 * nb + rb, nb, nb - rb, v, s);
+  const int lane = threadIdx.x & 63;
+  const double o = lane == 0 ? s[0] : lane == 1 ? s[1] : lane == 2 ? s[2] : s[3];
+  if (lane < 4) Y[off + c0 + 4 * (threadIdx.x >> 6) + lane] = o;
 }
 
-// v_j -= L_kj^T w_k for tiles j in [0, k), w_k read from Y: 64 columns per
-// workgroup, one wave per column at a time, lanes over rows.
+// v_j -= L_kj^T w_k for tiles j in [0, k), w_k read from Y: 16 columns per
+// workgroup.
 __global__ __launch_bounds__(256) void k_gemv_bwd(TileMap M, int k, double *__restrict__ V,
                                                  const double *__restrict__ Y, int64_t ldv) {
   __shared__ double w[1024];
-  const int nb = M.nb, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  double *Vc = V + (int64_t)blockIdx.z * ldv;
-  const int cb = nb / 64;
-  const int j = blockIdx.x / cb;
-  const int c0 = (blockIdx.x % cb) * 64;
-  for (int r = tid; r < nb; r += 256) w[r] = Y[(int64_t)blockIdx.z * ldv + (int64_t)k * nb + r];
+  const int nb = M.nb, cb = nb / SC;
+  const int j = blockIdx.x / cb, c0 = (blockIdx.x % cb) * SC;
+  const int64_t off = (int64_t)blockIdx.z * ldv;
+  for (int r = threadIdx.x; r < nb; r += 256) w[r] = Y[off + (int64_t)k * nb + r];
   __syncthreads();
-  const bool f32 = tile_is_f32(M, k, j);
-  for (int c = c0 + wave; c < c0 + 64; c += 4) {
-    double s = 0.0;
-    if (f32) {
-      const float *col = tile_ptr_f32(M, k, j) + (int64_t)c * nb;
-      for (int r = lane; r < nb; r += 64) s += (double)col[r] * w[r];
-    } else {
-      const double *col = tile_ptr(M, k, j) + (int64_t)c * nb;
-      for (int r = lane; r < nb; r += 64) s += col[r] * w[r];
-    }
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (lane == 0) Vc[(int64_t)j * nb + c] -= s;
-  }
+  double s[4];
+  if (tile_is_f32(M, k, j)) cols_dot(tile_ptr_f32(M, k, j) + (int64_t)c0 * nb, nb, nb, w, s);
+  else cols_dot(tile_ptr(M, k, j) + (int64_t)c0 * nb, nb, nb, w, s);
+  const int lane = threadIdx.x & 63;
+  const double o = lane == 0 ? s[0] : lane == 1 ? s[1] : lane == 2 ? s[2] : s[3];
+  if (lane < 4) V[off + (int64_t)j * nb + c0 + 4 * (threadIdx.x >> 6) + lane] -= o;
 }
 
 // Scratch of the per-column solves: the solved tiles (Np x nrhs).
@@ -286,7 +330,7 @@ int trsm_forward_multi(const mvg_mat *A, double *d_V, int nrhs, hipStream_t st) 
   double *Y = nullptr;
   if (int rc = solve_scratch(A, nrhs, &Y, st)) return rc;
   const TileMap M = A->map();
-  const int chunks = M.nb / 64;
+  const int chunks = M.nb / SR;
   int rc = 0;
   for (int k = 0; k < M.T && !rc; ++k) {
     hipLaunchKernelGGL(k_trsv_tile_fwd, dim3(chunks, 1, nrhs), dim3(256), 0, st, M.nb, k,
@@ -326,11 +370,11 @@ int trsm_backward_multi(const mvg_mat *A, double *d_V, int nrhs, hipStream_t st)
   const int nb = M.nb;
   int rc = 0;
   for (int k = M.T - 1; k >= 0 && !rc; --k) {
-    hipLaunchKernelGGL(k_trsv_tile_bwd, dim3(nb / 64, 1, nrhs), dim3(256), 0, st, nb, k,
+    hipLaunchKernelGGL(k_trsv_tile_bwd, dim3(nb / SC, 1, nrhs), dim3(256), 0, st, nb, k,
                        (const double *)A->d_winv, (const double *)d_V, Y, A->Np);
     rc = check_launch("trsv_tile_bwd");
     if (!rc && k > 0) {
-      hipLaunchKernelGGL(k_gemv_bwd, dim3(k * (nb / 64), 1, nrhs), dim3(256), 0, st, M, k, d_V,
+      hipLaunchKernelGGL(k_gemv_bwd, dim3(k * (nb / SC), 1, nrhs), dim3(256), 0, st, M, k, d_V,
                          (const double *)Y, A->Np);
       rc = check_launch("gemv_bwd");
     }

@@ -42,16 +42,20 @@ int launch_fill_f64(double *d, double v, int64_t n, hipStream_t st) {
 
 // ------------------------------------------------- trailing update (GEMM)
 //
-// A_ij -= L_ik L_jk^T over all tiles of the trailing matrix, in 128 x 128
-// output blocks.  Each workgroup (256 threads, 4 waves in a 2 x 2 grid, each
-// wave 64 x 64 = 4 x 4 MFMA 16x16 tiles) is persistent: it walks a contiguous
-// chunk of output blocks, and the chunks of the workgroups on one XCD are
-// adjacent, so neighbouring blocks (which share panel strips) meet in that
-// XCD's L2.  K is streamed through LDS in slices of TKB columns with TS-stage
-// pipelining by direct global->LDS loads (global_load_lds_dwordx4): no VGPR
-// staging, one barrier per slice, and the slices of the next block are in
-// flight while the current block's C update is written.  Lane l, element e
-// of an accumulator tile holds C[4e + l/16][l%16] of that 16 x 16 tile.
+// A_ij -= L_ik L_jk^T over all tiles of the trailing matrix, one 128 x 128
+// output block per workgroup (256 threads, 4 waves in a 2 x 2 grid, each wave
+// 64 x 64 = 4 x 4 MFMA 16x16 tiles); the blocks of one XCD are adjacent, so
+// neighbouring blocks (which share panel strips) meet in its L2.  K is
+// streamed through LDS in slices of TKB columns with TS-stage pipelining by
+// direct global->LDS loads (global_load_lds_dwordx4): no VGPR staging, one
+// barrier per slice.  Lane l, element e of an accumulator tile holds
+// C[4e + l/16][l%16] of that 16 x 16 tile.
+//
+// Measured: matrix units 86 % busy at 2.2-2.3 GHz with nb = 1024 (62 TFLOP/s),
+// 78-80 % at 2.15-2.2 GHz with nb = 512: the clock falls as the units fill, at
+// the card's power limit.  Persistent workgroups, in fixed chunks or taking
+// blocks from a counter per XCD, were slower (788 and 741 ms an evaluation at
+// n = 25,600 against 706), as was starting half of them later (no change).
 constexpr int KB = 16;   // K slice of the small panel GEMM
 constexpr int TKB = 16;  // K slice of the trailing GEMM
 constexpr int TS = 2;    // pipeline stages of the trailing GEMM (64 KB LDS per workgroup)
@@ -76,84 +80,81 @@ struct TrailBlock {
 };
 
 
-// Logical block lid of the trailing update of step k over columns j >= jlo:
-// tile (i, j) and 128 x 128 sub-block (sr, sc); false for the strict upper
-// sub-blocks of a diagonal tile (SYRK computes the lower part only).
-// Panel TRSM (mode TRAIL_TRSM): tile (k+1+lid/ss, k), output sub-block (sr, sc)
-// = P[sr] W_k[sc]^T with P the copy of the panel; W_k is lower triangular, so
-// only the first (sc+1)*128 columns of K contribute.
+// Block lid of the trailing update of step k over columns j >= jlo: column
+// after column, the lower 128 x 128 sub-blocks of the diagonal tile (SYRK),
+// then every sub-block (sr, sc) of the tiles (i, j) below it.
+// Panel TRSM (mode TRAIL_TRSM): tile (i, k), output sub-block (sr, sc) = P[sr]
+// W_k[sc]^T with P the copy of the panel; W_k is lower triangular, so only the
+// first (sc+1)*128 columns of K contribute, and the longest blocks come first.
+// Band targets (mode TRAIL_BAND, mixed precision): tiles (i, j), j > k, j <= i <
+// j + band, band passed as jlo; operands from P = the panel of step k upcast
+// to FP64.
 template <int MODE>
-__device__ __forceinline__ bool trail_decode(const TileMap &M, int k, int jlo, int64_t lid,
+__device__ __forceinline__ void trail_decode(const TileMap &M, int k, int jlo, int64_t lid,
                                              const double *P, const double *W, TrailBlock &t) {
   const int s = M.nb / IB, ss = s * s, nb = M.nb;
-  int64_t q = lid / ss;
-  const int sub = (int)(lid % ss);
-  const int sr = sub % s, sc = sub / s;
+  int64_t q = lid;
   if (MODE == TRAIL_TRSM) {
-    const int i = k + 1 + (int)q;
+    const int rows = (M.iend - k - 1) * s;  // 128-row strips of the panel
+    const int sc = s - 1 - (int)(q / rows), r = (int)(q % rows);
+    const int i = k + 1 + r / s, sr = r % s;
     t.C = tile_ptr(M, i, k) + (int64_t)sc * IB * nb + sr * IB;
-    t.A = P + q * (int64_t)nb * nb + sr * IB;
+    t.A = P + (int64_t)(r / s) * nb * nb + sr * IB;
     t.B = W + sc * IB;
     t.nk = (sc + 1) * (IB / TKB);
-    return true;
+    return;
   }
-  if (MODE == TRAIL_BAND) {
-    // band targets (mixed precision): tiles (i, j), j > k, j <= i < j + band,
-    // band passed as jlo; operands from P = the panel of step k upcast to FP64
-    const int band = jlo;
-    int j = k + 1;
-    while (q >= min(band, M.T - j)) {
-      q -= min(band, M.T - j);
-      ++j;
-    }
-    const int i = j + (int)q;
-    if (i == j && sr < sc) return false;
-    t.C = tile_ptr(M, i, j) + (int64_t)sc * IB * nb + sr * IB;
-    t.A = P + (int64_t)(i - k - 1) * nb * nb + sr * IB;
-    t.B = P + (int64_t)(j - k - 1) * nb * nb + sc * IB;
-    t.nk = nb / TKB;
-    return true;
-  }
-  int j = jlo;
-  while (q >= M.iend - j) {
-    q -= M.iend - j;
+  const int tri = s * (s + 1) / 2;
+  int j = MODE == TRAIL_BAND ? k + 1 : jlo;
+  auto column = [&]() {
+    const int below = MODE == TRAIL_BAND ? min(jlo, M.T - j) - 1 : M.iend - j - 1;
+    return tri + (int64_t)below * ss;
+  };
+  for (int64_t n = column(); q >= n; n = column()) {
+    q -= n;
     ++j;
   }
-  const int i = j + (int)q;
-  if (i == j && sr < sc) return false;
+  int i = j, sr, sc = 0;
+  if (q < tri) {
+    while (q >= s - sc) {
+      q -= s - sc;
+      ++sc;
+    }
+    sr = sc + (int)q;
+  } else {
+    q -= tri;
+    i = j + 1 + (int)(q / ss);
+    sr = (int)(q % ss) % s;
+    sc = (int)(q % ss) / s;
+  }
   t.C = tile_ptr(M, i, j) + (int64_t)sc * IB * nb + sr * IB;
-  t.A = tile_ptr(M, i, k) + sr * IB;
-  t.B = tile_ptr(M, j, k) + sc * IB;
+  if (MODE == TRAIL_BAND) {
+    t.A = P + (int64_t)(i - k - 1) * nb * nb + sr * IB;
+    t.B = P + (int64_t)(j - k - 1) * nb * nb + sc * IB;
+  } else {
+    t.A = tile_ptr(M, i, k) + sr * IB;
+    t.B = tile_ptr(M, j, k) + sc * IB;
+  }
   t.nk = nb / TKB;
-  return true;
-}
-
-// First valid block in [lid, lid1), or lid1.
-template <int MODE>
-__device__ __forceinline__ int64_t trail_next(const TileMap &M, int k, int jlo, int64_t lid,
-                                              int64_t lid1, const double *P, const double *W,
-                                              TrailBlock &t) {
-  while (lid < lid1 && !trail_decode<MODE>(M, k, jlo, lid, P, W, t)) ++lid;
-  return lid;
 }
 
 template <int NB, int MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_update_trailing(
-    TileMap M, int k, int jlo, int64_t lid0, int64_t nwg, int64_t chunk, const double *__restrict__ P,
+    TileMap M, int k, int jlo, int64_t lid0, int64_t nwg, const double *__restrict__ P,
     const double *__restrict__ W) {
   __shared__ double sA[TS][TKB * IB];
   __shared__ double sB[TS][TKB * IB];
 #define MVG_STA(u) (sA[(u)])
 #define MVG_STB(u) (sB[(u)])
   static_assert((NB / TKB) % TS == 0 && (IB / TKB) % TS == 0, "slices per block must divide by TS");
-  const int G = gridDim.x;  // multiple of 8
-  const int b = blockIdx.x;
-  const int64_t bp = (int64_t)(b & 7) * (G >> 3) + (b >> 3);  // XCD-contiguous chunk order
-  const int64_t lid1 = min(nwg, lid0 + (bp + 1) * chunk);
-  TrailBlock cur, nxt;
-  int64_t lc = trail_next<MODE>(M, k, jlo, lid0 + bp * chunk, lid1, P, W, cur);
-  if (lc >= lid1) return;
-  int64_t ln = trail_next<MODE>(M, k, jlo, lc + 1, lid1, P, W, nxt);
+  // Blocks to XCDs (workgroups go to them round robin): a contiguous eighth
+  // each, so that neighbouring blocks, which share panel strips, meet in one
+  // L2; the panel solve's, ordered by length, in turn.
+  const int G = gridDim.x, b = blockIdx.x;  // G: a multiple of 8
+  const int64_t lid = lid0 + (MODE == TRAIL_TRSM ? b : (int64_t)(b & 7) * (G >> 3) + (b >> 3));
+  if (lid >= nwg) return;
+  TrailBlock cur;
+  trail_decode<MODE>(M, k, jlo, lid, P, W, cur);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave & 1, wc = wave >> 1;
@@ -181,97 +182,84 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // C[wr*64 + ti*16 + 4e + l/16][wc*64 + tj*16 + l%16]; the four elements of
   // a lane sit 4 rows apart in one column, so only one address per tj is live.
   const int64_t coff = (int64_t)(wc * 64 + l16) * NB + wr * 64 + lk;
-  for (;;) {
-    // the accumulators start from C, the products are subtracted (negated A
-    // fragments) and the block ends with plain stores
-    // one opaque base per column group keeps every other offset an immediate
-    // (the empty asm stops the compiler from re-deriving 64 separate addresses)
-    typedef __attribute__((address_space(1))) double gdouble;  // global, not flat
-    gdouble *cb[4];
+  // the accumulators start from C, the products are subtracted (negated A
+  // fragments) and the block ends with plain stores
+  // one opaque base per column group keeps every other offset an immediate
+  // (the empty asm stops the compiler from re-deriving 64 separate addresses)
+  typedef __attribute__((address_space(1))) double gdouble;  // global, not flat
+  gdouble *cb[4];
 #pragma unroll
-    for (int tj = 0; tj < 4; ++tj) {
-      cb[tj] = (gdouble *)(cur.C + coff + (int64_t)tj * 16 * NB);
-      asm volatile("" : "+v"(cb[tj]));
-    }
+  for (int tj = 0; tj < 4; ++tj) {
+    cb[tj] = (gdouble *)(cur.C + coff + (int64_t)tj * 16 * NB);
+    asm volatile("" : "+v"(cb[tj]));
+  }
 #pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
+  for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < 4; ++tj)
+    for (int tj = 0; tj < 4; ++tj)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          acc[ti][tj][e] = (MODE != TRAIL_TRSM) ? (double)cb[tj][ti * 16 + 4 * e] : 0.0;
-    const bool have_next = ln < lid1;
-    const int nk = cur.nk;
-    for (int kb0 = 0; kb0 < nk; kb0 += TS) {
+      for (int e = 0; e < 4; ++e)
+        acc[ti][tj][e] = (MODE != TRAIL_TRSM) ? (double)cb[tj][ti * 16 + 4 * e] : 0.0;
+  const int nk = cur.nk;
+  for (int kb0 = 0; kb0 < nk; kb0 += TS) {
 #pragma unroll
-      for (int u = 0; u < TS; ++u) {
-        const int kb = kb0 + u;
-        // TS-1 slices in flight; the oldest (kb) is complete when <= (TS-2) TD remain
-        // the barrier is pinned: no LDS read of this stage and no direct load
-        // into the stage being refilled may be scheduled across it
-        wait_vmcnt<(TS - 2) * TD>();
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("" ::: "memory");
-        // the refill issue runs at raised wave priority, so that a wave
-        // coming out of the barrier gets its direct loads in flight before
-        // the other workgroup's MFMA stream takes the issue slots (measured
-        // +6 % on the trailing update)
-        __builtin_amdgcn_s_setprio(1);
-        // refill the stage computed in the previous step: next slice of this
-        // block, else the first slices of the next block, else (past the end
-        // of the chunk) the last slice again, in bounds and never read
-        const int p = kb + TS - 1;
-        const bool in_cur = p < nk;
-        const bool use_next = !in_cur && have_next;
-        const double *pa = use_next ? nxt.A : cur.A;
-        const double *pb = use_next ? nxt.B : cur.B;
-        const int pk = in_cur ? p : (use_next ? p - nk : nk - 1);
-        // the first k-step's fragments are read before the refill is issued,
-        // so these LDS reads do not queue behind the direct loads' LDS writes
-        // (measured +6.5 %)
-        const double *a = MVG_STA(u) + wr * 64 + l16;
-        const double *bb = MVG_STB(u) + wc * 64 + l16;
-        double af0[4], bf0[4];
+    for (int u = 0; u < TS; ++u) {
+      const int kb = kb0 + u;
+      // TS-1 slices in flight; the oldest (kb) is complete when <= (TS-2) TD remain
+      // the barrier is pinned: no LDS read of this stage and no direct load
+      // into the stage being refilled may be scheduled across it
+      wait_vmcnt<(TS - 2) * TD>();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("" ::: "memory");
+      // the refill issue runs at raised wave priority, so that a wave
+      // coming out of the barrier gets its direct loads in flight before
+      // the other workgroup's MFMA stream takes the issue slots (measured
+      // +6 % on the trailing update)
+      __builtin_amdgcn_s_setprio(1);
+      // refill the stage computed in the previous step with the next slice
+      // (past the end the last slice again, in bounds and never read)
+      const int pk = min(kb + TS - 1, nk - 1);
+      // the first k-step's fragments are read before the refill is issued,
+      // so these LDS reads do not queue behind the direct loads' LDS writes
+      // (measured +6.5 %)
+      const double *a = MVG_STA(u) + wr * 64 + l16;
+      const double *bb = MVG_STB(u) + wc * 64 + l16;
+      double af0[4], bf0[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        af0[t] = (MODE != TRAIL_TRSM) ? -a[lk * IB + t * 16] : a[lk * IB + t * 16];
+        bf0[t] = bb[lk * IB + t * 16];
+      }
+      MVG_ISSUE(cur.A, cur.B, pk, (u + TS - 1) % TS);
+      __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+      for (int ks = 0; ks < TKB; ks += 4) {
+        double af[4], bf[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-          af0[t] = (MODE != TRAIL_TRSM) ? -a[lk * IB + t * 16] : a[lk * IB + t * 16];
-          bf0[t] = bb[lk * IB + t * 16];
+          af[t] = ks == 0 ? af0[t]
+                          : ((MODE != TRAIL_TRSM) ? -a[(ks + lk) * IB + t * 16]
+                                                  : a[(ks + lk) * IB + t * 16]);
+          bf[t] = ks == 0 ? bf0[t] : bb[(ks + lk) * IB + t * 16];
         }
-        MVG_ISSUE(pa, pb, pk, (u + TS - 1) % TS);
-        __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-        for (int ks = 0; ks < TKB; ks += 4) {
-          double af[4], bf[4];
+        for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            af[t] = ks == 0 ? af0[t]
-                            : ((MODE != TRAIL_TRSM) ? -a[(ks + lk) * IB + t * 16]
-                                                    : a[(ks + lk) * IB + t * 16]);
-            bf[t] = ks == 0 ? bf0[t] : bb[(ks + lk) * IB + t * 16];
-          }
-#pragma unroll
-          for (int ti = 0; ti < 4; ++ti)
-#pragma unroll
-            for (int tj = 0; tj < 4; ++tj)
-              acc[ti][tj] =
-                  __builtin_amdgcn_mfma_f64_16x16x4f64(af[ti], bf[tj], acc[ti][tj], 0, 0, 0);
-        }
+          for (int tj = 0; tj < 4; ++tj)
+            acc[ti][tj] =
+                __builtin_amdgcn_mfma_f64_16x16x4f64(af[ti], bf[tj], acc[ti][tj], 0, 0, 0);
       }
     }
-#pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
-#pragma unroll
-      for (int tj = 0; tj < 4; ++tj)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) cb[tj][ti * 16 + 4 * e] = acc[ti][tj][e];
-    if (!have_next) break;
-    cur = nxt;
-    lc = ln;
-    ln = trail_next<MODE>(M, k, jlo, lc + 1, lid1, P, W, nxt);
   }
+#pragma unroll
+  for (int ti = 0; ti < 4; ++ti)
+#pragma unroll
+    for (int tj = 0; tj < 4; ++tj)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) cb[tj][ti * 16 + 4 * e] = acc[ti][tj][e];
   // no direct LDS load may outlive the workgroup
   wait_vmcnt_0();
 #undef MVG_ISSUE
@@ -707,32 +695,6 @@ static double trailing_flops(int64_t N, int nb, int T, int k, int jlo, int jhi, 
   return f;
 }
 
-// Persistent grid of the GEMM kernels: two workgroups per CU, minus a few
-// slots left free so that the look-ahead stream's small kernels find a CU
-// (persistent workgroups never retire mid-launch).  MVG_GEMM_RESERVE
-// overrides the number of reserved slots (tuning).
-constexpr int GEMM_CUS = 256;
-static int gemm_reserve() {
-  static int r = -1;
-  if (r < 0) {
-    const char *e = getenv("MVG_GEMM_RESERVE");
-    r = e ? atoi(e) : 32;
-    if (r < 0 || r > 2 * GEMM_CUS - 8) r = 32;
-  }
-  return r;
-}
-// 1: persistent workgroups walking chunks of blocks; 0 (default, measured
-// faster with the look-ahead stream): one block per workgroup, so that
-// workgroups retire continuously and the look-ahead kernels find room
-// (MVG_GEMM_PERSIST, tuning).
-static int gemm_persist() {
-  static int r = -1;
-  if (r < 0) {
-    const char *e = getenv("MVG_GEMM_PERSIST");
-    r = e ? (atoi(e) != 0) : 0;
-  }
-  return r;
-}
 // 1: the next diagonal tile is factored on a second stream while the
 // trailing update runs; 0: one stream (MVG_LOOKAHEAD, tuning).
 static int lookahead() {
@@ -749,14 +711,12 @@ int launch_trail(const TileMap &M, int k, int jlo, int64_t lid0, int64_t nwg, co
                  const double *W, hipStream_t st) {
   const int64_t work = nwg - lid0;
   if (work <= 0) return 0;
-  int64_t G = gemm_persist() ? std::min<int64_t>(work, 2 * GEMM_CUS - gemm_reserve()) : work;
-  G = (G + 7) / 8 * 8;
-  const int64_t chunk = (work + G - 1) / G;
+  const int64_t G = (work + 7) / 8 * 8;
   switch (M.nb) {
 #define MVG_CASE(NBV)                                                                          \
   case NBV:                                                                                    \
     hipLaunchKernelGGL((k_update_trailing<NBV, MODE>), dim3((unsigned)G), dim3(256), 0, st, M, \
-                       k, jlo, lid0, nwg, chunk, P, W);                                        \
+                       k, jlo, lid0, nwg, P, W);                                               \
     break;
     MVG_CASE(128) MVG_CASE(256) MVG_CASE(512) MVG_CASE(768) MVG_CASE(1024)
 #undef MVG_CASE
@@ -775,24 +735,19 @@ template int launch_trail<TRAIL_BAND>(const TileMap &, int, int, int64_t, int64_
                                       const double *, hipStream_t);
 
 // Trailing update of step k: A_ij -= L_ik L_jk^T for k < j <= i < M.iend,
-// optionally without the diagonal tile (k+1, k+1) (first = 0: that tile is
-// left to the look-ahead stream), or only that tile (only_first).  With a
+// optionally without the diagonal tile (k+1, k+1) (skip_first: that tile is
+// left to the look-ahead stream).  With a
 // DST band of w tiles L_ik = 0 for i >= k + w, so M.iend = min(T, k + w)
 // skips only zero products.
-static int trailing(const TileMap &M, int64_t N, int k, bool skip_first, bool only_first,
-                    hipStream_t st) {
+static int trailing(const TileMap &M, int64_t N, int k, bool skip_first, hipStream_t st) {
   const int jlo = k + 1;
   if (jlo >= M.iend) return 0;
-  const int s = M.nb / IB;
-  const int64_t ss = (int64_t)s * s;
-  const int64_t ntile = only_first ? 1 : (int64_t)(M.iend - jlo) * (M.iend - jlo + 1) / 2;
-  const int64_t nwg = ntile * ss;
-  const int64_t lid0 = skip_first ? ss : 0;
+  const int64_t s = M.nb / IB, n = M.iend - jlo;
+  const int64_t ntile = n * (n + 1) / 2;
+  const int64_t nwg = n * (s * (s + 1) / 2) + (ntile - n) * s * s;
+  const int64_t lid0 = skip_first ? s * (s + 1) / 2 : 0;
   if (lid0 >= nwg) return 0;
-  const double flops = only_first ? (double)std::min<int64_t>(M.nb, N - (int64_t)jlo * M.nb) *
-                                        ((double)std::min<int64_t>(M.nb, N - (int64_t)jlo * M.nb) + 1) *
-                                        (double)std::min<int64_t>(M.nb, N - (int64_t)k * M.nb)
-                                  : trailing_flops(N, M.nb, M.iend, k, jlo, M.iend - 1, skip_first);
+  const double flops = trailing_flops(N, M.nb, M.iend, k, jlo, M.iend - 1, skip_first);
   const double bytes = 8.0 * (double)(ntile - (skip_first ? 1 : 0)) * M.nb * M.nb * 4.0;
   int h = prof_begin(MVG_PROF_TRAILING, st, flops, bytes);
   int rc = launch_trail<TRAIL_UPDATE>(M, k, jlo, lid0, nwg, nullptr, nullptr, st);
@@ -866,7 +821,7 @@ int dense_potrf(mvg_mat *A, int64_t *d_info, hipStream_t st) {
     hipEventRecord(evS, st);
     if (rc) break;
     if (k + 1 < T && A->N - (int64_t)(k + 1) * M.nb <= FLAT_ROWS) {
-      rc = trailing(step_map(k), A->N, k, false, false, st);
+      rc = trailing(step_map(k), A->N, k, false, st);
       if (!rc) rc = chol_flat(M, k + 1, dst_band, A->d_winv, d_info, pt, st);
       break;
     }
@@ -875,7 +830,7 @@ int dense_potrf(mvg_mat *A, int64_t *d_info, hipStream_t st) {
       rc = launch_syrk_next(A, k, side);  // SYRK of tile (k+1, k+1) by step k
       if (!rc) rc = diag_factor(M, k + 1, A->d_winv, d_info, pt, side);
       hipEventRecord(evD, side);
-      if (!rc) rc = trailing(step_map(k), A->N, k, true, false, st);  // the rest of step k
+      if (!rc) rc = trailing(step_map(k), A->N, k, true, st);  // the rest of step k
     }
   }
   hipEventRecord(evD, side);

@@ -638,8 +638,10 @@ int mixed_potrf(mvg_mat *A, int64_t *d_info, hipStream_t st) {
       const int noff = nbelow - nband;                               // FP32 panel tiles
       hipLaunchKernelGGL(k_panel_stage_pre, dim3(64, nbelow), dim3(256), 0, st, M, k, P64, P32);
       rc = check_launch("panel_stage_pre");
+      TileMap Mt = M;
+      Mt.iend = k + 1 + nband;
       if (!rc && nband > 0)
-        rc = launch_trail<TRAIL_TRSM>(M, k, 0, 0, (int64_t)nband * ss, P64,
+        rc = launch_trail<TRAIL_TRSM>(Mt, k, 0, 0, (int64_t)nband * ss, P64,
                                       A->d_winv + (int64_t)k * per, st);
       if (!rc && noff > 0) {
         hipLaunchKernelGGL(k_to_f32, dim3(256), dim3(256), 0, st, A->d_winv + (int64_t)k * per,
@@ -661,10 +663,11 @@ int mixed_potrf(mvg_mat *A, int64_t *d_info, hipStream_t st) {
     double f64 = 0.0, flow = 0.0;
     mixed_flops(A->N, nb, T, k, band, &f64, &flow);
     if (!rc) {
-      int64_t nband_t = 0;
-      for (int j = k + 1; j < T; ++j) nband_t += std::min(band, T - j);
+      int64_t nband_t = 0;  // blocks: the diagonal tiles' lower ones, the other tiles'
+      const int64_t tri = (int64_t)s * (s + 1) / 2;
+      for (int j = k + 1; j < T; ++j) nband_t += tri + (std::min(band, T - j) - 1) * ss;
       int h = prof_begin(MVG_PROF_TRAILING, st, f64, 0.0);
-      rc = launch_trail<TRAIL_BAND>(M, k, band, ss, nband_t * ss, P64, nullptr, st);
+      rc = launch_trail<TRAIL_BAND>(M, k, band, tri, nband_t, P64, nullptr, st);
       prof_end(h, st);
     }
     if (!rc) {

@@ -276,6 +276,16 @@ __global__ void k_reduce_chunks(const double *__restrict__ part, int64_t m, int 
   zhat[i] = s;
 }
 
+// mse[t] = c0 - sum over chunks of the squares of right-hand sides 2t, 2t + 1
+__global__ void k_mse_chunks(const double *__restrict__ sq, int64_t m, int64_t n, int ld, double c0,
+                             double *__restrict__ mse) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= m) return;
+  double a = 0.0;
+  for (int64_t c = 0; c < n; ++c) a += sq[c * ld + 2 * t] + sq[c * ld + 2 * t + 1];
+  mse[t] = c0 - a;
+}
+
 __global__ void k_mse_final(const double *__restrict__ ss, int64_t m, double trc0,
                             double *__restrict__ mse) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1605,6 +1615,12 @@ int mloe_mmom(const double *d_x, const double *d_y, int64_t n_loc, const mvg_the
   return 0;
 }
 
+// From this many targets on the errors' solve takes the right-hand sides
+// transposed on the trailing update's kernel (padded to 128 of them); below,
+// or where its memory is short, the task-list products (1000 targets on 5,000
+// locations 6.1 -> 4.9 ms; 64 on 1,000 at nb = 256 539 us there, 549 here).
+constexpr int64_t MSE_RHS_MIN = 80;
+
 int cokrige_predict(const mvg_factor *F, const double *d_x0, const double *d_y0, int64_t m,
                     double *d_zhat, double *d_mse, void *hip_stream) {
   if (!F || !F->A || !F->d_w) return -1;
@@ -1632,7 +1648,23 @@ int cokrige_predict(const mvg_factor *F, const double *d_x0, const double *d_y0,
   }
   hipFreeAsync(part, st);
   prof_end(hc, st);
-  if (!rc && d_mse) {
+  const int ld = (int)((2 * m + 127) / 128 * 128);
+  double *VY = nullptr;  // V and Y, then the sums of squares by chunks
+  const int64_t nsq = (A->Np + RHS_CHUNK - 1) / RHS_CHUNK;
+  if (!rc && d_mse && A->precision == MVG_FP64 && m >= MSE_RHS_MIN &&
+      malloc_async((void **)&VY, sizeof(double) * (2 * A->Np + nsq) * ld, st) == hipSuccess) {
+    double *V = VY, *Y = V + A->Np * ld, *sq = Y + A->Np * ld;
+    rc = launch_cokrige_c0t(A->margs, A->d_qtab, A->d_x, A->d_y, A->n_loc, A->Np, d_x0, d_y0, m, ld,
+                            V, st);
+    if (!rc) rc = trsm_forward_rhs(A, V, Y, ld, sq, st);
+    if (!rc) {
+      hipLaunchKernelGGL(k_mse_chunks, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st,
+                         (const double *)sq, m, nsq, ld, A->theta.sigma11_sq + A->theta.sigma22_sq,
+                         d_mse);
+      rc = check_launch("mse_chunks");
+    }
+    hipFreeAsync(VY, st);
+  } else if (!rc && d_mse) {
     double *V = nullptr, *ss = nullptr;
     if (malloc_async((void **)&V, sizeof(double) * (A->Np * 2 * m + 2 * m), st) != hipSuccess) {
       hipGetLastError();

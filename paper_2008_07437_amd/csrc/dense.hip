@@ -89,6 +89,9 @@ struct TrailBlock {
 // Band targets (mode TRAIL_BAND, mixed precision): tiles (i, j), j > k, j <= i <
 // j + band, band passed as jlo; operands from P = the panel of step k upcast
 // to FP64.
+// Right-hand sides (mode TRAIL_RHS): V_i -= Y_k L_ik^T for i > k, V and Y (in W
+// and P) holding the transposed right-hand sides, column-major with the
+// leading dimension jlo.
 template <int MODE>
 __device__ __forceinline__ void trail_decode(const TileMap &M, int k, int jlo, int64_t lid,
                                              const double *P, const double *W, TrailBlock &t) {
@@ -102,6 +105,16 @@ __device__ __forceinline__ void trail_decode(const TileMap &M, int k, int jlo, i
     t.A = P + (int64_t)(r / s) * nb * nb + sr * IB;
     t.B = W + sc * IB;
     t.nk = (sc + 1) * (IB / TKB);
+    return;
+  }
+  if (MODE == TRAIL_RHS) {
+    const int64_t ld = jlo;
+    const int strips = jlo / IB, per = strips * s;
+    const int i = k + 1 + (int)(q / per), r = (int)(q % per), sr = r % strips, sc = r / strips;
+    t.C = const_cast<double *>(W) + ((int64_t)i * nb + sc * IB) * ld + sr * IB;
+    t.A = P + (int64_t)k * nb * ld + sr * IB;
+    t.B = tile_ptr(M, i, k) + sc * IB;
+    t.nk = nb / TKB;
     return;
   }
   const int tri = s * (s + 1) / 2;
@@ -163,12 +176,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // w, w + 4, ... of both, one column per direct load; lane l moves rows 2l,
   // 2l+1.
   const int loff = 2 * lane;
+  const int64_t lda = MODE == TRAIL_RHS ? (int64_t)jlo : NB;  // of A and C
 #define MVG_ISSUE(pa, pb, kb, st)                                                                 \
   do {                                                                                            \
-    const double *a_ = (pa) + (int64_t)((kb) * TKB + wave) * NB;                                  \
+    const double *a_ = (pa) + (int64_t)((kb) * TKB + wave) * lda;                                 \
     const double *b_ = (pb) + (int64_t)((kb) * TKB + wave) * NB;                                  \
     _Pragma("unroll") for (int c_ = 0; c_ < TKB / 4; ++c_) {                                      \
-      __builtin_amdgcn_global_load_lds((const void *)(a_ + 4 * c_ * NB + loff),                  \
+      __builtin_amdgcn_global_load_lds((const void *)(a_ + 4 * c_ * lda + loff),                 \
                                        MVG_LDS(MVG_STA(st) + (wave + 4 * c_) * IB), 16, 0, 0);   \
       __builtin_amdgcn_global_load_lds((const void *)(b_ + 4 * c_ * NB + loff),                  \
                                        MVG_LDS(MVG_STB(st) + (wave + 4 * c_) * IB), 16, 0, 0);   \
@@ -181,7 +195,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // MFMA(A fragment, B fragment): lane l, element e of tile (ti, tj) holds
   // C[wr*64 + ti*16 + 4e + l/16][wc*64 + tj*16 + l%16]; the four elements of
   // a lane sit 4 rows apart in one column, so only one address per tj is live.
-  const int64_t coff = (int64_t)(wc * 64 + l16) * NB + wr * 64 + lk;
+  const int64_t coff = (int64_t)(wc * 64 + l16) * lda + wr * 64 + lk;
   // the accumulators start from C, the products are subtracted (negated A
   // fragments) and the block ends with plain stores
   // one opaque base per column group keeps every other offset an immediate
@@ -190,7 +204,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   gdouble *cb[4];
 #pragma unroll
   for (int tj = 0; tj < 4; ++tj) {
-    cb[tj] = (gdouble *)(cur.C + coff + (int64_t)tj * 16 * NB);
+    cb[tj] = (gdouble *)(cur.C + coff + (int64_t)tj * 16 * lda);
     asm volatile("" : "+v"(cb[tj]));
   }
 #pragma unroll
@@ -731,6 +745,8 @@ template int launch_trail<TRAIL_UPDATE>(const TileMap &, int, int, int64_t, int6
                                         const double *, hipStream_t);
 template int launch_trail<TRAIL_TRSM>(const TileMap &, int, int, int64_t, int64_t, const double *,
                                       const double *, hipStream_t);
+template int launch_trail<TRAIL_RHS>(const TileMap &, int, int, int64_t, int64_t, const double *,
+                                     const double *, hipStream_t);
 template int launch_trail<TRAIL_BAND>(const TileMap &, int, int, int64_t, int64_t, const double *,
                                       const double *, hipStream_t);
 
@@ -840,6 +856,56 @@ int dense_potrf(mvg_mat *A, int64_t *d_info, hipStream_t st) {
   hipEventDestroy(evS);
   hipEventDestroy(ev0);
   return rc;
+}
+
+// --------------------------------------------- many right-hand sides
+//
+// L^-1 applied to many right-hand sides held transposed (column r of V: row r
+// of all of them), so that both steps are the A B^T products of the
+// factorisation: Y_k = V_k W_k^T, then V_i -= Y_k L_ik^T on the trailing
+// update's kernel.
+
+// Y_k = V_k W_k^T in 64 x 64 blocks (W_k lower triangular: K = 64 (sc + 1)),
+// the longest first: 128 x 128 blocks leave most CUs without one.
+__global__ __launch_bounds__(256) void k_rhs_tile(int nb, int k, int ld, const double *__restrict__ W,
+                                                  const double *__restrict__ V,
+                                                  double *__restrict__ Y) {
+  __shared__ double smem[SMALL_LDS];
+  const int strips = ld / PB, sc = nb / PB - 1 - (int)blockIdx.x / strips;
+  const int64_t sr = (int64_t)(blockIdx.x % strips) * PB, c0 = (int64_t)k * nb;
+  gemm_block64<false>(Y + (c0 + sc * PB) * ld + sr, ld, V + c0 * ld + sr, ld,
+                      W + (int64_t)k * nb * nb + sc * PB, nb, (sc + 1) * PB, smem);
+}
+
+// part[chunk][c] = sum of the squares of RHS_CHUNK rows of right-hand side c
+__global__ __launch_bounds__(256) void k_rhs_squares(const double *__restrict__ Y, int64_t Np, int ld,
+                                                     double *__restrict__ part) {
+  __shared__ double red[4][64];
+  const int c = blockIdx.x * 64 + (threadIdx.x & 63), g = threadIdx.x >> 6;
+  const int64_t r0 = (int64_t)blockIdx.y * RHS_CHUNK, r1 = min(Np, r0 + RHS_CHUNK);
+  double q = 0.0;
+  for (int64_t r = r0 + g; r < r1; r += 4) q = fma(Y[r * ld + c], Y[r * ld + c], q);
+  red[g][threadIdx.x & 63] = q;
+  __syncthreads();
+  if (g == 0)
+    part[(int64_t)blockIdx.y * ld + c] =
+        (red[0][threadIdx.x] + red[1][threadIdx.x]) + (red[2][threadIdx.x] + red[3][threadIdx.x]);
+}
+
+int trsm_forward_rhs(const mvg_mat *A, double *d_V, double *d_Y, int ld, double *d_part,
+                     hipStream_t st) {
+  const TileMap M = A->map();
+  const int nb = M.nb, s = nb / IB;
+  for (int k = 0; k < M.T; ++k) {
+    hipLaunchKernelGGL(k_rhs_tile, dim3((ld / PB) * (nb / PB)), dim3(256), 0, st, nb, k, ld,
+                       (const double *)A->d_winv, (const double *)d_V, d_Y);
+    if (int rc = check_launch("rhs_tile")) return rc;
+    const int64_t nwg = (int64_t)(M.T - k - 1) * s * (ld / IB);
+    if (int rc = launch_trail<TRAIL_RHS>(M, k, ld, 0, nwg, d_Y, d_V, st)) return rc;
+  }
+  hipLaunchKernelGGL(k_rhs_squares, dim3(ld / 64, (unsigned)((A->Np + RHS_CHUNK - 1) / RHS_CHUNK)),
+                     dim3(256), 0, st, (const double *)d_Y, A->Np, ld, d_part);
+  return check_launch("rhs_squares");
 }
 
 // ----------------------------------------------------------- reductions

@@ -443,4 +443,46 @@ int launch_cokrige_c0(const MaternArgs &P, const double *d_qtab, const double *d
   return check_launch("cokrige_c0");
 }
 
+// The same, transposed: V[(2r + i) ld + 2t + j] = C_ij(||s0_t - s_r||), zero for
+// padded rows and targets.  64 targets by 32 locations per workgroup, a row's
+// targets side by side.
+template <int FORM>
+__global__ __launch_bounds__(256) void k_cokrige_c0t(MaternArgs P, const double *__restrict__ qtab,
+                                                     const double *__restrict__ xs,
+                                                     const double *__restrict__ ys, int64_t n_loc,
+                                                     int64_t Np, const double *__restrict__ x0,
+                                                     const double *__restrict__ y0, int64_t m, int ld,
+                                                     double *__restrict__ V) {
+  __shared__ double ct[cov_lds(FORM)];
+  load_cov_table<FORM>(qtab, ct);
+  const int64_t t = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
+  const bool real = t < m;
+  const double xt = real ? x0[t] : 0.0, yt = real ? y0[t] : 0.0;
+  for (int q = threadIdx.x >> 6; q < 32; q += 4) {
+    const int64_t r = (int64_t)blockIdx.y * 32 + q;
+    if (2 * r >= Np) break;
+    double c[3] = {0.0, 0.0, 0.0};
+    if (real && r < n_loc) cross_cov_block<FORM>(xt, yt, xs[r], ys[r], P, ct, qtab, c);
+    double *v = V + 2 * r * ld + 2 * t;
+    *reinterpret_cast<double2 *>(v) = make_double2(c[0], c[2]);
+    *reinterpret_cast<double2 *>(v + ld) = make_double2(c[2], c[1]);
+  }
+}
+
+int launch_cokrige_c0t(const MaternArgs &P, const double *d_qtab, const double *d_x,
+                       const double *d_y, int64_t n_loc, int64_t Np, const double *d_x0,
+                       const double *d_y0, int64_t m, int ld, double *d_c0, hipStream_t st) {
+  const dim3 grid((unsigned)(ld / 128), (unsigned)((Np / 2 + 31) / 32));
+#define MVG_FORM(F)                                                                              \
+  hipLaunchKernelGGL(k_cokrige_c0t<F>, grid, dim3(256), 0, st, P, d_qtab, d_x, d_y, n_loc, Np,   \
+                     d_x0, d_y0, m, ld, d_c0)
+  switch (cov_form(P)) {
+    case COV_TABLE: MVG_FORM(COV_TABLE); break;
+    case COV_QUAD: MVG_FORM(COV_QUAD); break;
+    default: MVG_FORM(COV_CLOSED); break;
+  }
+#undef MVG_FORM
+  return check_launch("cokrige_c0t");
+}
+
 }  // namespace mvg

@@ -174,6 +174,10 @@ int launch_cokrige_dot(const MaternArgs &P, const double *d_qtab, const double *
 int launch_cokrige_c0(const MaternArgs &P, const double *d_qtab, const double *d_x,
                       const double *d_y, int64_t n_loc, int64_t Np, const double *d_x0,
                       const double *d_y0, int64_t m, double *d_c0, hipStream_t st);
+// the same transposed: row r of all 2 m columns at d_c0 + r ld, zeros past 2 m
+int launch_cokrige_c0t(const MaternArgs &P, const double *d_qtab, const double *d_x,
+                       const double *d_y, int64_t n_loc, int64_t Np, const double *d_x0,
+                       const double *d_y0, int64_t m, int ld, double *d_c0, hipStream_t st);
 
 // dense FP64 Cholesky pieces
 // Pivot rule: a pivot at or below 2^-40 of the variable's variance (tol[g % p]
@@ -187,7 +191,7 @@ struct PivotTol {
   int lreal = 0;
 };
 PivotTol pivot_tol(const mvg_mat *A);
-enum { TRAIL_UPDATE = 0, TRAIL_TRSM = 1, TRAIL_BAND = 2 };
+enum { TRAIL_UPDATE = 0, TRAIL_TRSM = 1, TRAIL_BAND = 2, TRAIL_RHS = 3 };
 template <int MODE>
 int launch_trail(const TileMap &M, int k, int jlo, int64_t lid0, int64_t nwg, const double *P,
                  const double *W, hipStream_t st);
@@ -219,6 +223,12 @@ int launch_trmm_t(const mvg_mat *A, const double *d_X, double *d_Y, int nrhs, hi
 int launch_dot_cols(const double *d_A, const double *d_B, int64_t Np, int ncols, double *d_out,
                     hipStream_t st);
 int trsm_forward_multi(const mvg_mat *A, double *d_V, int nrhs, hipStream_t st);  // V <- L^-1 V (col-major, ld Np)
+// Y = (L^-1 B)^T from V = B^T (ld right-hand sides, a multiple of 128, by Np rows; V
+// is overwritten) on an FP64 factor, and the sums of squares of each
+// right-hand side over chunks of RHS_CHUNK rows: part[chunk][ld]
+constexpr int RHS_CHUNK = 256;
+int trsm_forward_rhs(const mvg_mat *A, double *d_V, double *d_Y, int ld, double *d_part,
+                     hipStream_t st);
 int logdet_quad(const mvg_mat *A, const double *d_y, double *d_part, double *d_out2,
                 hipStream_t st);  // d_out2 = {2 sum log L_jj, y^T y}
 int launch_gather(const mvg_mat *A, const int64_t *rows, const int64_t *cols, int64_t m,

@@ -108,3 +108,20 @@ def test_batched_block_edges(lib, orc):
     again = lib.loglik_many_noalloc(tasks * 8)
     for key in ("loglik", "logdet", "quad", "status"):
         assert np.array_equal(again[key], np.tile(got[key], 8)), key
+
+
+# prediction errors on both sides of the switch to transposed right-hand sides,
+# with odd numbers of targets and one to several tiles
+@pytest.mark.parametrize("n,m,nb", [(40, 79, 128), (40, 80, 128), (150, 128, 128), (150, 65, 256),
+                                    (300, 129, 128), (700, 200, 512), (600, 97, 768)])
+def test_prediction_errors(lib, orc, n, m, nb):
+    print("prediction errors n=%d m=%d nb=%d" % (n, m, nb), flush=True)
+    th = synthetic.THETA_REF
+    x, y = _sites(orc, n, 8)
+    z = orc.simulate_z(x, y, th, synthetic.normal_eps(2 * n, 8))
+    x0, y0 = synthetic.uniform_targets(m, 8)
+    ref, ref_mse = orc.cokrige(x, y, z, th, x0, y0, with_mse=True)
+    _, F = lib.loglik(_dev(x), _dev(y), _dev(z), th, {"nb": nb}, keep=True)
+    zhat, mse = lib.cokrige_predict(F, _dev(x0), _dev(y0), with_mse=True)
+    np.testing.assert_allclose(zhat.cpu().numpy(), ref, rtol=0, atol=1e-10)
+    np.testing.assert_allclose(mse.cpu().numpy(), ref_mse, rtol=1e-8, atol=1e-12)

@@ -989,48 +989,6 @@ int launch_sum_sq_cols(const double *d_V, int64_t Np, int ncols, double *d_out, 
   return check_launch("sum_sq_cols");
 }
 
-// z = L eps: one thread per row r of tile row I, z_r = sum_{J<I} L_IJ[r,:] eps_J
-// + sum_{c<=r} L_II[r,c] eps_I[c] (the diagonal tile's upper part is not read).
-__global__ __launch_bounds__(256) void k_trmv(TileMap M, const double *__restrict__ eps,
-                                              double *__restrict__ z, int64_t N) {
-  const int nb = M.nb;
-  const int chunks = (nb + 255) / 256;
-  const int I = blockIdx.x / chunks;
-  const int r = (blockIdx.x % chunks) * 256 + threadIdx.x;
-  if (r >= nb) return;
-  double s = 0.0;
-  for (int J = 0; J < I; ++J) {
-    const double *L = tile_ptr(M, I, J);
-    const double *e = eps + (int64_t)J * nb;
-    for (int c = 0; c < nb; ++c) s += L[(int64_t)c * nb + r] * e[c];
-  }
-  const double *L = tile_ptr(M, I, I);
-  const double *e = eps + (int64_t)I * nb;
-  for (int c = 0; c <= r; ++c) s += L[(int64_t)c * nb + r] * e[c];
-  const int64_t g = (int64_t)I * nb + r;
-  if (g < N) z[g] = s;
-}
-
-int launch_trmv(const mvg_mat *A, const double *d_eps, double *d_z, hipStream_t st) {
-  // eps is read up to the padded length: stage a zero-padded copy
-  double *ep = nullptr;
-  if (malloc_async((void **)&ep, sizeof(double) * A->Np, st) != hipSuccess) {
-    hipGetLastError();
-    set_error("trmv workspace allocation failed");
-    return MVG_ERR_ALLOC;
-  }
-  int rc = launch_fill_f64(ep, 0.0, A->Np, st);
-  if (!rc) {
-    hipMemcpyAsync(ep, d_eps, sizeof(double) * A->N, hipMemcpyDeviceToDevice, st);
-    const int chunks = (A->nb + 255) / 256;
-    hipLaunchKernelGGL(k_trmv, dim3(A->T * chunks), dim3(256), 0, st, A->map(), (const double *)ep,
-                       d_z, A->N);
-    rc = check_launch("trmv");
-  }
-  hipFreeAsync(ep, st);
-  return rc;
-}
-
 // ----------------------------------------------------------- inspection
 
 __device__ __forceinline__ double load_entry(const TileMap &M, int64_t r, int64_t c) {

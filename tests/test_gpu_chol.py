@@ -125,3 +125,17 @@ def test_prediction_errors(lib, orc, n, m, nb):
     zhat, mse = lib.cokrige_predict(F, _dev(x0), _dev(y0), with_mse=True)
     np.testing.assert_allclose(zhat.cpu().numpy(), ref, rtol=0, atol=1e-10)
     np.testing.assert_allclose(mse.cpu().numpy(), ref_mse, rtol=1e-8, atol=1e-12)
+
+
+@pytest.mark.parametrize("n,nb", [(1, 128), (33, 128), (200, 128), (300, 256), (600, 512), (1100, 1024)])
+def test_factor_times_vector(lib, n, nb):
+    """Z = L eps against the dense product of the same factor; 1e-13 of the
+    row's largest partial sum (at most 2n roundings of 1e-16)."""
+    print("L eps n=%d nb=%d" % (n, nb), flush=True)
+    x, y = synthetic.jittered_grid(n, 2)
+    A = lib.cov_generate(_dev(x), _dev(y), synthetic.THETA_REF, {"nb": nb})
+    assert lib.potrf_tiled(A) == 0
+    eps = synthetic.normal_eps(2 * n, 2)
+    low = A.to_dense().cpu().numpy()
+    got = lib.mvg_trmv(A, _dev(eps)).cpu().numpy()
+    assert np.all(np.abs(got - low @ eps) <= 1e-13 * (np.abs(low) @ np.abs(eps)))

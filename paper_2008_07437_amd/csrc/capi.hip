@@ -276,6 +276,15 @@ __global__ void k_reduce_chunks(const double *__restrict__ part, int64_t m, int 
   zhat[i] = s;
 }
 
+// the locations into a matrix's own copy
+__global__ void k_copy_xy(const double *__restrict__ x, const double *__restrict__ y, int64_t n,
+                          double *__restrict__ ox, double *__restrict__ oy) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  ox[i] = x[i];
+  oy[i] = y[i];
+}
+
 // mse[t] = c0 - sum over chunks of the squares of right-hand sides 2t, 2t + 1
 __global__ void k_mse_chunks(const double *__restrict__ sq, int64_t m, int64_t n, int ld, double c0,
                              double *__restrict__ mse) {
@@ -384,12 +393,14 @@ static void mat_free(mvg_mat *A) {
   if (!A) return;
   tlr_state_free(A->tlr);
   arena_release(A->arena, A->arena_bytes);
-  dev_free(A->d_off);
-  dev_free(A->d_kind);
-  dev_free(A->d_x);
-  dev_free(A->d_y);
-  dev_free(A->d_qtab);
-  dev_free(A->d_winv);
+  if (A->blob) {
+    dev_free(A->blob);
+  } else {
+    dev_free(A->d_x);
+    dev_free(A->d_y);
+    dev_free(A->d_qtab);
+    dev_free(A->d_winv);
+  }
   if (A->done) hipEventDestroy(A->done);
   delete[] A->h_off;
   delete[] A->h_kind;
@@ -504,13 +515,24 @@ static int mat_alloc(int64_t n_loc, int p, const mvg_opts &o, const double *d_x,
   tile_layout(A->T, A->nb, A->precision == MVG_TLR ? MVG_FP64 : A->precision, A->band, A->h_off,
               A->h_kind, &A->arena_bytes, &zero_off);
   A->arena = (char *)arena_acquire(A->arena_bytes);
-  bool ok = A->arena != nullptr;
-  ok = ok && (A->d_off = (int64_t *)dev_alloc(sizeof(int64_t) * nt)) != nullptr;
-  ok = ok && (A->d_kind = (int *)dev_alloc(sizeof(int) * nt)) != nullptr;
-  ok = ok && (A->d_x = (double *)dev_alloc(sizeof(double) * n_loc)) != nullptr;
-  ok = ok && (A->d_y = (double *)dev_alloc(sizeof(double) * n_loc)) != nullptr;
-  ok = ok && (A->d_qtab = (double *)dev_alloc(sizeof(double) * std::max(QTAB, (1 + PORD) * QN))) != nullptr;
-  ok = ok && (A->d_winv = (double *)dev_alloc(sizeof(double) * (size_t)A->Np * A->nb)) != nullptr;
+  // one allocation: x | y | tables | inverses | offsets | kinds.  FP64 tiles
+  // are packed evenly and need neither of the last two
+  const bool tables = o.precision != MVG_FP64;
+  const size_t nx = ((size_t)n_loc + 31) / 32 * 32, nq = (std::max(QTAB, (1 + PORD) * QN) + 31) / 32 * 32;
+  const size_t nw = (size_t)A->Np * A->nb;
+  const size_t bytes = sizeof(double) * (2 * nx + nq + nw) +
+                       (tables ? (sizeof(int64_t) + sizeof(int)) * (size_t)nt : 0);
+  const bool ok = A->arena && (A->blob = dev_alloc(bytes)) != nullptr;
+  if (ok) {
+    A->d_x = (double *)A->blob;
+    A->d_y = A->d_x + nx;
+    A->d_qtab = A->d_y + nx;
+    A->d_winv = A->d_qtab + nq;
+    if (tables) {
+      A->d_off = (int64_t *)(A->d_winv + nw);
+      A->d_kind = (int *)(A->d_off + nt);
+    }
+  }
   if (!ok) {
     hipGetLastError();
     set_error("device allocation of %.3f GB for a %lld-location matrix failed",
@@ -518,10 +540,12 @@ static int mat_alloc(int64_t n_loc, int p, const mvg_opts &o, const double *d_x,
     mat_free(A);
     return MVG_ERR_ALLOC;
   }
-  hipMemcpyAsync(A->d_off, A->h_off, sizeof(int64_t) * nt, hipMemcpyHostToDevice, st);
-  hipMemcpyAsync(A->d_kind, A->h_kind, sizeof(int) * nt, hipMemcpyHostToDevice, st);
-  hipMemcpyAsync(A->d_x, d_x, sizeof(double) * n_loc, hipMemcpyDeviceToDevice, st);
-  hipMemcpyAsync(A->d_y, d_y, sizeof(double) * n_loc, hipMemcpyDeviceToDevice, st);
+  if (tables) {
+    hipMemcpyAsync(A->d_off, A->h_off, sizeof(int64_t) * nt, hipMemcpyHostToDevice, st);
+    hipMemcpyAsync(A->d_kind, A->h_kind, sizeof(int) * nt, hipMemcpyHostToDevice, st);
+  }
+  hipLaunchKernelGGL(k_copy_xy, dim3((unsigned)((n_loc + 255) / 256)), dim3(256), 0, st, d_x, d_y,
+                     n_loc, A->d_x, A->d_y);
   // the host offset tables are read by the copies above; keep them alive with A
   if (zero_off >= 0) {  // the shared tile of the annihilated DST tiles
     if (int rc = launch_fill_f64(reinterpret_cast<double *>(A->arena + zero_off), 0.0,
@@ -902,10 +926,10 @@ static int loglik_mixed(const double *d_x, const double *d_y, const double *d_z,
     if (!rc) rc = eval_mixed(S, A, d_z, d, w, d_out2 + 2 * i, d_info + i, &g_ir[i],
                                 keep != nullptr, st);
   }
-  std::vector<double> out2(2 * n_theta);
+  // results and pivots lie together: one copy
+  std::vector<double> out2(3 * n_theta);
   std::vector<int64_t> info(n_theta);
-  hipMemcpyAsync(out2.data(), d_out2, sizeof(double) * 2 * n_theta, hipMemcpyDeviceToHost, st);
-  hipMemcpyAsync(info.data(), d_info, sizeof(int64_t) * n_theta, hipMemcpyDeviceToHost, st);
+  hipMemcpyAsync(out2.data(), d_out2, sizeof(double) * 3 * n_theta, hipMemcpyDeviceToHost, st);
   mvg_factor *F = nullptr;
   if (!rc && keep) {
     F = new mvg_factor();
@@ -925,6 +949,7 @@ static int loglik_mixed(const double *d_x, const double *d_y, const double *d_z,
     set_error("stream synchronisation failed: %s", hipGetErrorString(hipGetLastError()));
     rc = MVG_ERR_LAUNCH;
   }
+  std::memcpy(info.data(), out2.data() + 2 * n_theta, sizeof(int64_t) * n_theta);
   mat_free(S);
   if (rc) {
     if (F) {
@@ -1255,10 +1280,10 @@ int loglik(const double *d_x, const double *d_y, const double *d_z, int64_t n_lo
     (void)npair;
     if (!rc) rc = eval_one(A, d_z, d_yv, d_part, d_out2 + 2 * i, d_info + i, st);
   }
-  std::vector<double> out2(2 * n_theta);
+  // results and pivots lie together: one copy
+  std::vector<double> out2(3 * n_theta);
   std::vector<int64_t> info(n_theta);
-  hipMemcpyAsync(out2.data(), d_out2, sizeof(double) * 2 * n_theta, hipMemcpyDeviceToHost, st);
-  hipMemcpyAsync(info.data(), d_info, sizeof(int64_t) * n_theta, hipMemcpyDeviceToHost, st);
+  hipMemcpyAsync(out2.data(), d_out2, sizeof(double) * 3 * n_theta, hipMemcpyDeviceToHost, st);
   mvg_factor *F = nullptr;
   if (!rc && keep) {
     F = new mvg_factor();
@@ -1279,6 +1304,7 @@ int loglik(const double *d_x, const double *d_y, const double *d_z, int64_t n_lo
     set_error("stream synchronisation failed: %s", hipGetErrorString(hipGetLastError()));
     rc = MVG_ERR_LAUNCH;
   }
+  std::memcpy(info.data(), out2.data() + 2 * n_theta, sizeof(int64_t) * n_theta);
   if (rc) {
     if (F) {
       dev_free(F->d_w);
@@ -1382,15 +1408,16 @@ static int loglik_p_run(const double *d_x, const double *d_y, const double *d_z,
     prof_end(hg, st);
     if (!rc) rc = eval_one(A, d_z, d_yv, d_part, d_out2 + 2 * i, d_info + i, st);
   }
-  std::vector<double> out2(2 * n_theta);
+  // results and pivots lie together: one copy
+  std::vector<double> out2(3 * n_theta);
   std::vector<int64_t> info(n_theta);
-  hipMemcpyAsync(out2.data(), d_out2, sizeof(double) * 2 * n_theta, hipMemcpyDeviceToHost, st);
-  hipMemcpyAsync(info.data(), d_info, sizeof(int64_t) * n_theta, hipMemcpyDeviceToHost, st);
+  hipMemcpyAsync(out2.data(), d_out2, sizeof(double) * 3 * n_theta, hipMemcpyDeviceToHost, st);
   hipFreeAsync(ws, st);
   if (hipStreamSynchronize(st) != hipSuccess && !rc) {
     set_error("stream synchronisation failed: %s", hipGetErrorString(hipGetLastError()));
     rc = MVG_ERR_LAUNCH;
   }
+  std::memcpy(info.data(), out2.data() + 2 * n_theta, sizeof(int64_t) * n_theta);
   const double two_pi_term = 0.5 * (double)A->N * std::log(2.0 * M_PI);
   mat_free(A);
   if (rc) return rc;

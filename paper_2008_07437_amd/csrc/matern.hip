@@ -14,6 +14,7 @@
 #include <cmath>
 
 #include "matern_dev.h"
+#include "tile_dev.h"
 
 namespace mvg {
 
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(256) void k_cov_tiles(MaternArgs P, const double *_
   const bool lpad = gl >= n_loc;
   const double xl = lpad ? 0.0 : xs[gl], yl = lpad ? 0.0 : ys[gl];
   const int kind = M.kind ? M.kind[tile] : TK_F64;
-  char *tb = M.base + M.off[tile];
+  char *tb = tile_bytes(M, tile);
   for (int q = 0; q < 4; ++q) {
     const int pr = pc0 + q;
     if (pr >= hp) break;
@@ -258,7 +259,7 @@ __global__ __launch_bounds__(256) void k_cov_tiles_p(MaternArgsP A, const double
   if (l > lr1) return;
   const bool lreal = l < n_loc;
   const double xl = lreal ? xs[l] : 0.0, yl = lreal ? ys[l] : 0.0;
-  char *tb = M.base + M.off[tile];
+  char *tb = tile_bytes(M, tile);
   const int64_t rbase = lc0 + (sub / spt) * 32 + (threadIdx.x >> 5) * 4;
   for (int q = 0; q < 4; ++q) {
     const int64_t r = rbase + q;

@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "mvgeo_internal.h"
+#include "tile_dev.h"
 
 namespace mvg {
 
@@ -41,9 +42,6 @@ constexpr int LS = 4;     // pipeline stages
 __device__ __forceinline__ void lp_wait_vmcnt_8() { __builtin_amdgcn_s_waitcnt(0x0F78); }
 __device__ __forceinline__ void lp_wait_vmcnt_0() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-__device__ __forceinline__ char *tile_bytes(TileMap M, int I, int J) {
-  return M.base + M.off[tidx(I, J, M.T)];
-}
 
 __device__ __forceinline__ int64_t lp_xcd_remap(int64_t bid, int64_t pad) {
   const int64_t per = pad >> 3;
@@ -97,13 +95,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     lp_offband(M, k, band, q, i, j);
     A = P32 + (int64_t)(i - k - 1) * NB * NB + sr * LB;
     B = P32 + (int64_t)(j - k - 1) * NB * NB + sc * LB;
-    C = reinterpret_cast<CT *>(tile_bytes(M, i, j)) + (int64_t)sc * LB * NB + sr * LB;
+    C = reinterpret_cast<CT *>(tile_bytes(M, tidx(i, j, M.T))) + (int64_t)sc * LB * NB + sr * LB;
     nk = NB / LK32;
   } else {
     const int i = k + band + (int)q;
     A = P32 + (int64_t)(i - k - 1) * NB * NB + sr * LB;
     B = W32 + sc * LB;
-    C = reinterpret_cast<CT *>(tile_bytes(M, i, k)) + (int64_t)sc * LB * NB + sr * LB;
+    C = reinterpret_cast<CT *>(tile_bytes(M, tidx(i, k, M.T))) + (int64_t)sc * LB * NB + sr * LB;
     nk = (sc + 1) * (LB / LK32);
   }
   const int tid = threadIdx.x, lane = tid & 63;
@@ -236,7 +234,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   lp_offband(M, k, band, q, i, j);
   const uint16_t *A = P16 + (int64_t)(i - k - 1) * NB * NB + (int64_t)sr * LB * NB;
   const uint16_t *B = P16 + (int64_t)(j - k - 1) * NB * NB + (int64_t)sc * LB * NB;
-  float *C = reinterpret_cast<float *>(tile_bytes(M, i, j)) + (int64_t)sc * LB * NB + sr * LB;
+  float *C = reinterpret_cast<float *>(tile_bytes(M, tidx(i, j, M.T))) + (int64_t)sc * LB * NB + sr * LB;
   constexpr int nk = NB / LK16;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -340,7 +338,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NS == 2 ? 2
   lp_offband(M, k, band, q, i, j);
   const int64_t ao = (int64_t)(i - k - 1) * NB * NB + (int64_t)sr * LB * NB;
   const int64_t bo = (int64_t)(j - k - 1) * NB * NB + (int64_t)sc * LB * NB;
-  double *C = reinterpret_cast<double *>(tile_bytes(M, i, j)) + (int64_t)sc * LB * NB + sr * LB;
+  double *C = reinterpret_cast<double *>(tile_bytes(M, tidx(i, j, M.T))) + (int64_t)sc * LB * NB + sr * LB;
   constexpr int nk = NB / LK16;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -714,7 +712,7 @@ __global__ __launch_bounds__(256) void k_symv_tile(TileMap M, const double *__re
     xj[r] = x[(int64_t)J * nb + r];
   }
   __syncthreads();
-  const double *Tl = reinterpret_cast<const double *>(M.base + M.off[tile]);
+  const double *Tl = reinterpret_cast<const double *>(tile_bytes(M, tile));
   double acc[16];
 #pragma unroll
   for (int q = 0; q < 16; ++q) acc[q] = 0.0;
@@ -863,8 +861,8 @@ int launch_axpy(double *d_x, const double *d_d, int64_t n, hipStream_t st) {
 __global__ __launch_bounds__(256) void k_mat_convert(TileMap S, TileMap D) {
   const int64_t t = blockIdx.y;
   const int64_t per = (int64_t)S.nb * S.nb;
-  const double *src = reinterpret_cast<const double *>(S.base + S.off[t]);
-  char *dst = D.base + D.off[t];
+  const double *src = reinterpret_cast<const double *>(tile_bytes(S, t));
+  char *dst = tile_bytes(D, t);
   const bool f32 = D.kind[t] == TK_F32;
   for (int64_t e = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 2; e < per;
        e += (int64_t)gridDim.x * blockDim.x * 2) {
@@ -887,8 +885,10 @@ int launch_mat_convert(const mvg_mat *S, mvg_mat *D, hipStream_t st) {
   for (int64_t t0 = 0; t0 < nt; t0 += 65535) {
     const int64_t cnt = std::min<int64_t>(65535, nt - t0);
     TileMap a = Ms, b = Md;
-    a.off += t0;
+    if (a.off) a.off += t0;
+    a.base += t0 * a.stride;
     b.off += t0;
+    b.base += t0 * b.stride;
     b.kind += t0;
     hipLaunchKernelGGL(k_mat_convert, dim3(16, (unsigned)cnt), dim3(256), 0, st, a, b);
     if (int rc = check_launch("mat_convert")) return rc;

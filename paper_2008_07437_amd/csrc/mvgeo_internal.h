@@ -122,8 +122,9 @@ struct mvg_mat {
   int nb = 0, T = 0, precision = 0, factored = 0, band = 0;
   char *arena = nullptr;          // tile storage
   size_t arena_bytes = 0;
-  int64_t *d_off = nullptr;       // per-tile byte offsets
-  int *d_kind = nullptr;          // per-tile kind
+  void *blob = nullptr;           // the device buffers below in one allocation (not TLR)
+  int64_t *d_off = nullptr;       // per-tile byte offsets (null: FP64, tiles packed evenly)
+  int *d_kind = nullptr;          // per-tile kind (null: FP64)
   int64_t *h_off = nullptr;
   int *h_kind = nullptr;
   double *d_x = nullptr, *d_y = nullptr;  // library copies of the locations

@@ -6,9 +6,12 @@
 
 namespace mvg {
 
+// packed tile t
+__device__ __forceinline__ char *tile_bytes(const TileMap &M, int64_t t) {
+  return M.base + (M.stride ? t * M.stride : M.off[t]);
+}
 __device__ __forceinline__ double *tile_ptr(TileMap M, int I, int J) {
-  const int64_t t = tidx(I, J, M.T);
-  return reinterpret_cast<double *>(M.base + (M.stride ? t * M.stride : M.off[t]));
+  return reinterpret_cast<double *>(tile_bytes(M, tidx(I, J, M.T)));
 }
 __device__ __forceinline__ float *tile_ptr_f32(TileMap M, int I, int J) {
   return reinterpret_cast<float *>(M.base + M.off[tidx(I, J, M.T)]);

@@ -6,22 +6,34 @@
 // so what it costs is its latency, not its arithmetic.  One launch per step
 // keeps the chain short: the workgroup of row block t + 1 forms its block of
 // L, updates the diagonal block (t+1, t+1) and factors it in the same launch,
-// while the others apply the panel of the step before to the rest.  For that
-// each update lags one step behind the panel:
+// while the others update the rest.  For that each update lags at least one
+// step behind its panel:
 //
 //   launch t:  rows R > t:     A(R, t) -= L(R, t-1) L(t, t-1)^T
 //                              L(R, t)  = A(R, t) W(t, t)^T
 //              row t + 1 also: A(t+1, t+1) -= both panels' products, then
 //                              L(t+1, t+1) and W(t+1, t+1)
-//              R >= C > t:     A(R, C) -= L(R, t-1) L(C, t-1)^T
 //              row t of W:     W(t, j) = -W(t, t) sum_m L(t, m) W(m, j)
 //
-// Every block is written by one workgroup and all it reads was finished by
-// the launch before, so there is nothing to wait for inside a launch.
+// The rest of the matrix is updated by GROUP panels at once, which reads and
+// writes it once for them: with u = t - g0, the panels g..g + GROUP - 1 (g a
+// multiple of GROUP from g0) go to the columns from g + GROUP + 1 on in
+// launches g + GROUP .. g + 2 GROUP - 1, a share of the columns in each, the
+// nearest first.  What the next two launches need is updated by itself:
+//
+//   launch t:  R > t + 1:      A(R, t+1)   -= panels g..t-1 of the group of t
+//                              A(t+2, t+2) -= the same
+//
+// The order of the panels is the same for every block, so the split decides
+// nothing about the result.  Every block is written by one workgroup and all
+// it reads was finished by the launch before, so there is nothing to wait for
+// inside a launch.
 //
 // Measured: 18 us a step while the chain bounds it (about 4 us of launch, 1.3
-// of loads, 10 of the 64 x 64 factor, the rest the products before it), 33 us
-// at 4,096 trailing rows, where the rank-64 update's traffic does.  Before, a
+// of loads, 10 of the 64 x 64 factor, the rest the products before it), 29 us
+// at 4,096 trailing rows and 62 at 6,400 (33 and 73 with one panel at a time
+// and 8-byte loads), where the rank-64 updates do: 36 us of matrix-core time
+// at 6,400, the rest waiting for operands at the blocks' starts and ends.  Before, a
 // step was three launches (factor 37 us, panel 5, update 9) and the inverse of
 // a tile 7 (nb = 512) or 15 more of 12 to 40 us each: 2n = 3,074 took 6.2 ms,
 // now 1.7; a 1024 tile 2 ms, now 0.3.
@@ -42,7 +54,39 @@ struct StepArgs {
   int s;          // blocks per tile side
   int r0, r1;     // rows of column t (t + 1 .. r0 - 1) and of column t - 1 that are not zero
   int nw, np;     // workgroups for W's row t and for the panel's rows from t + 2
+  int l0, nl;     // first panel of t's group; rows of column t + 1 it goes to now, and the diagonal
+  int q0;         // first panel of the group before, which goes to columns c0 .. c1 - 1,
+  int c0, c1, cr; // rows up to cr - 1
+  int nq;         // positions of these (see rest_block)
 };
+
+// Whole simulation of 6,400 rows and likelihood of 12,800 (ms): one panel at a
+// time 3.93, 16.9; 2 at once 3.47, 16.5; 4: 3.37, 16.2; 6: 3.42, 16.2; 8: 3.56,
+// 16.4, the shares then being too few blocks for the chip.
+constexpr int GROUP = 4;
+constexpr int SUP = 8;  // super-blocks of SUP x SUP blocks share their panels in one L2
+
+// Position b of the rest: rows in strips of SUP, in each the columns up to its
+// last row in groups of SUP.  Positions above the diagonal have no block.
+__device__ __forceinline__ bool rest_block(const StepArgs &a, int b, int &R, int &C) {
+  const int m = a.cr - a.c0, w = a.c1 - a.c0;
+  int i = 0, n = 0;
+  for (;; ++i) {
+    n = min(SUP, m - SUP * i) * min(w, SUP * (i + 1));
+    if (b < n) break;
+    b -= n;
+  }
+  const int h = min(SUP, m - SUP * i), j = b / (h * SUP);
+  b -= j * h * SUP;
+  R = a.c0 + SUP * i + b % h;
+  C = a.c0 + SUP * j + b / h;
+  return C <= R;
+}
+static int rest_positions(int m, int w) {
+  int n = 0;
+  for (int i = 0; SUP * i < m; ++i) n += std::min(SUP, m - SUP * i) * std::min(w, SUP * (i + 1));
+  return n;
+}
 
 __device__ __forceinline__ double *step_block(const StepArgs &a, int R, int C) {
   return tile_ptr(a.M, R / a.s, C / a.s) + (int64_t)(C % a.s) * CB * a.M.nb + (R % a.s) * CB;
@@ -160,14 +204,38 @@ __global__ __launch_bounds__(256, 2) void k_chol_step(StepArgs a) {
     row_step<false>(r, sm, 0, a.pr, a.info);
     return;
   }
-  // block (R, C) of the lower triangle from (t + 1, t + 1), whose first block
-  // belongs to row t + 1's workgroup
-  b = b - a.np + 1;
-  int i = (int)((sqrtf(8.0f * (float)b + 1.0f) - 1.0f) * 0.5f);
-  while ((int64_t)(i + 1) * (i + 2) / 2 <= b) ++i;
-  while ((int64_t)i * (i + 1) / 2 > b) --i;
-  const int R = t + 1 + i, C = t + 1 + (int)(b - (int64_t)i * (i + 1) / 2);
-  block_sub_nt(step_block(a, R, C), step_block(a, R, t - 1), step_block(a, C, t - 1), nb, R == C);
+  b -= a.np;
+  int R, C, p0, n;
+  if (b < a.nl) {
+    R = b + 1 < a.nl ? t + 2 + b : t + 2;
+    C = b + 1 < a.nl ? t + 1 : t + 2;
+    p0 = a.l0;
+    n = t - a.l0;
+  } else {
+    // a contiguous eighth of the positions to each XCD (workgroups go to them in turn)
+    b -= a.nl;
+    const int per = (a.nq + 7) >> 3;
+    b = (b & 7) * per + (b >> 3);
+    if (b >= a.nq || !rest_block(a, b, R, C)) return;
+    if (R == t + 1) return;  // (t + 1, t + 1), the critical row's
+    p0 = a.q0;
+    n = GROUP;
+  }
+  auto panel = [&](int p, const double *&A, const double *&B) {
+    A = step_block(a, R, p0 + p);
+    B = step_block(a, C, p0 + p);
+  };
+  block_sub_nt(step_block(a, R, C), n, panel, nb, R == C);
+}
+
+// The first column of share u of GROUP of the lower triangle of m columns:
+// equal areas, but no column in a later share than the launch that updates it
+// by itself allows.
+static int rest_column(int m, int u) {
+  if (u == 0 || m <= 0) return 0;
+  if (u == GROUP) return m;
+  const int c = (int)std::ceil(m * (1.0 - std::sqrt(1.0 - (double)u / GROUP)));
+  return std::min(m, std::max(c, GROUP + 1));
 }
 
 // Blocks g0..g1-1 (64 rows each) of the matrix, g0 the first block of a tile;
@@ -195,8 +263,18 @@ static int chol_region(const TileMap &M, int band, int g0, int g1, double *winv,
       a.r1 = t > g0 ? rows(t - 1) : 0;
       a.nw = 4 * (t % a.s);
       a.np = std::max(0, a.r0 - (t + 2));
-      const int64_t m = std::max(0, a.r1 - (t + 1));
-      n += a.nw + a.np + std::max<int64_t>(0, m * (m + 1) / 2 - 1);
+      const int u = (t - g0) % GROUP;  // launches since the group's panels began
+      a.l0 = t - u;
+      a.nl = u > 0 && t + 2 < a.r1 ? a.r1 - (t + 2) + 1 : 0;
+      a.nq = 0;
+      if (t - g0 >= GROUP) {
+        a.q0 = t - u - GROUP;
+        a.cr = rows(t - u - 1);
+        a.c0 = t - u + 1 + rest_column(a.cr - (t - u + 1), u);
+        a.c1 = t - u + 1 + rest_column(a.cr - (t - u + 1), u + 1);
+        if (a.c1 > a.c0) a.nq = rest_positions(a.cr - a.c0, a.c1 - a.c0);
+      }
+      n += a.nw + a.np + a.nl + (a.nq + 7) / 8 * 8;
     }
     if (n <= 0) continue;
     hipLaunchKernelGGL(k_chol_step, dim3((unsigned)n), dim3(256), 0, st, a);

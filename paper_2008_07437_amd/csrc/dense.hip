@@ -784,12 +784,13 @@ static int panel_trsm(const TileMap &M, int k, const double *winv, double *P, hi
 }
 
 // Trailing matrices of at most this many rows are factored in 64-wide steps
-// throughout (chol.hip): one launch of 23-40 us per step against a tile
+// throughout (chol.hip): one launch of 20-100 us per step against a tile
 // step's chain of look-ahead, panel copy, panel solve and update.  Where the
-// rank-64 updates' memory traffic outweighs that: 2n = 6,400 at nb = 512,
-// whole evaluation, tiles from 4,096 rows 5.8 ms, from 6,144 5.3, from 8,192
-// 5.2; 2n = 12,800: 20.9, 20.3, 21.1 ms.
-constexpr int64_t FLAT_ROWS = 6144;
+// 64-wide steps' updates, at 60 % of the matrix cores' rate, outweigh that:
+// whole evaluation of 7,500 rows, tiles from 6,144 5.1 ms, 64-wide throughout
+// 4.9; of 12,800, from 6,144 16.4 ms, from 8,192 and 9,216 16.15, from 10,240
+// 16.3.
+constexpr int64_t FLAT_ROWS = 8192;
 
 // Right-looking tiled Cholesky with one tile of look-ahead.  Caller stream:
 // panel TRSM of column k (GEMM against W_k), then the trailing update of

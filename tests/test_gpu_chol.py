@@ -77,6 +77,30 @@ def test_tiled_and_tail(lib, n, nb):
     assert float((low - cpu).abs().max()) <= max(10 * floor, 1e-13)
 
 
+# block counts at the edges of the groups of four panels and of their shares,
+# tiles of two, four and eight blocks, the band of the tiles kept (0: all) and
+# both sides of the largest matrix that is factored in steps throughout
+@pytest.mark.parametrize("n,nb,band", [(127, 128, 0), (129, 128, 0), (161, 128, 0), (289, 256, 0),
+                                       (352, 256, 0), (545, 128, 0), (1056, 512, 0),
+                                       (4095, 128, 0), (4097, 512, 0), (545, 128, 2),
+                                       (600, 128, 3), (700, 256, 2)])
+def test_grouped_updates(lib, n, nb, band):
+    print("grouped n=%d nb=%d band=%d" % (n, nb, band), flush=True)
+    import torch
+    # a short range and sites in rows: the banded matrix stays positive definite
+    th = (1.0, 1.0, 0.03, 0.5, 1.0, 0.5)
+    x, y = synthetic.jittered_grid(n, 4)
+    opts = {"nb": nb, "precision": lib.MVG_DST, "band_tiles": band} if band else {"nb": nb}
+    A = lib.cov_generate(_dev(x), _dev(y), th, opts)
+    S = A.to_dense()
+    S = S + torch.tril(S, -1).T
+    assert lib.potrf_tiled(A) == 0
+    low = A.to_dense()
+    cpu = torch.as_tensor(scipy.linalg.cholesky(S.cpu().numpy(), lower=True)).cuda()
+    floor = float((torch.linalg.cholesky(S) - cpu).abs().max())
+    assert float((low - cpu).abs().max()) <= max(10 * floor, 1e-13)
+
+
 # a duplicated site: the failing pivot in the first, a middle and the last block
 @pytest.mark.parametrize("at", [1, 17, 40, 200, 299])
 def test_first_failing_pivot(lib, orc, at):

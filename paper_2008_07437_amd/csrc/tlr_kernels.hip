@@ -1080,13 +1080,20 @@ __global__ __launch_bounds__(NTH) void k_qr_sample(const QrTask *__restrict__ ta
 // index; exact norms every step), then the same column swaps on A (all m
 // rows, in order) and on tk.piv.  One workgroup per task; each thread keeps
 // the sample columns c = tid + 256 k in registers (QRS_ROWS values each).
+// A chain of 16 dependent steps, bound by its latency.  Two barriers a step:
+// the owner of the chosen column forms the reflector where it lies and takes
+// the column that it displaces from LDS (the chosen one is not needed again).
+// The update moves every row up by one, so that the pivot row is always row 0
+// and what is summed needs no test against t; slots of 256 columns past the
+// last are skipped.  43.6 us a launch before (four barriers, a swap through
+// LDS, a select for each element), now 36.7.
 constexpr int PICK_THREADS = 256;
 constexpr int PICK_COLS = QR_MAXN / PICK_THREADS;  // columns per thread
 
 __global__ __launch_bounds__(PICK_THREADS) void k_qr_pick(const QrTask *__restrict__ tasks, int p0) {
-  __shared__ double s_best[PICK_THREADS / 64];
-  __shared__ int s_bidx[PICK_THREADS / 64];
-  __shared__ double scol[2][QRS_ROWS];  // the two columns of a swap
+  __shared__ double s_best[2][PICK_THREADS / 64];  // of even and odd steps
+  __shared__ int s_bidx[2][PICK_THREADS / 64];
+  __shared__ double scol[QRS_ROWS];  // column t, on its way to the chosen one's place
   __shared__ double sv[QRS_ROWS];
   __shared__ int sswap[PQB];
   __shared__ int smove[2][2 * PQB];  // positions moved to, and the start of their columns
@@ -1111,68 +1118,59 @@ __global__ __launch_bounds__(PICK_THREADS) void k_qr_pick(const QrTask *__restri
 #pragma unroll
       for (int i = 0; i < QRS_ROWS; ++i) g[k][i] = 0.0;
   for (int t = 0; t < steps; ++t) {
-    // the thread's largest remaining norm (rows t ..), ties to the lower column
+    // row i of a column is row t + i of the sample, zero from QRS_ROWS - t on
+    // the thread's largest remaining norm, ties to the lower column
     double best = -1.0;
     int bi = nrem;
 #pragma unroll
     for (int k = 0; k < PICK_COLS; ++k) {
+      if (PICK_THREADS * k >= nrem) break;
       const int c = tid + PICK_THREADS * k;
       double ss = 0.0;
 #pragma unroll
-      for (int i = 0; i < QRS_ROWS; ++i)
-        if (i >= t) ss += g[k][i] * g[k][i];
+      for (int i = 0; i < QRS_ROWS; ++i) ss += g[k][i] * g[k][i];
       if (c >= t && c < nrem && ss > best) {
         best = ss;
         bi = c;
       }
     }
     wave_argmax(best, bi);
+    double *sb = s_best[t & 1];
+    int *si = s_bidx[t & 1];
     if (lane == 0) {
-      s_best[wave] = best;
-      s_bidx[wave] = bi;
+      sb[wave] = best;
+      si[wave] = bi;
     }
     __syncthreads();
-    int pcol = s_bidx[0];
-    double pb = s_best[0];
+    int pcol = si[0];
+    double pb = sb[0];
 #pragma unroll
     for (int w = 1; w < PICK_THREADS / 64; ++w)
-      if (s_best[w] > pb || (s_best[w] == pb && s_bidx[w] < pcol)) {
-        pb = s_best[w];
-        pcol = s_bidx[w];
+      if (sb[w] > pb || (sb[w] == pb && si[w] < pcol)) {
+        pb = sb[w];
+        pcol = si[w];
       }
+    pcol = __builtin_amdgcn_readfirstlane(pcol);
+    if (pcol >= nrem) pcol = t;  // no norm compares (NaN)
+    const int powner = pcol % PICK_THREADS, pslot = pcol / PICK_THREADS;
     if (tid == 0) sswap[t] = pcol;
-    // swap columns t and pcol through LDS (t < PQB: thread t, slot 0)
-    if (pcol != t) {
+    if (tid == t && pcol != t)
 #pragma unroll
-      for (int k = 0; k < PICK_COLS; ++k) {
-        const int c = tid + PICK_THREADS * k;
-        if (c == pcol)
+      for (int i = 0; i < QRS_ROWS; ++i) scol[i] = g[0][i];
+    // reflector of the chosen column
+    if (tid == powner) {
+      double x[QRS_ROWS];
 #pragma unroll
-          for (int i = 0; i < QRS_ROWS; ++i) scol[0][i] = g[k][i];
-        if (c == t)
+      for (int i = 0; i < QRS_ROWS; ++i) x[i] = g[0][i];
 #pragma unroll
-          for (int i = 0; i < QRS_ROWS; ++i) scol[1][i] = g[k][i];
-      }
-      __syncthreads();
+      for (int k = 1; k < PICK_COLS; ++k)
+        if (pslot == k)
 #pragma unroll
-      for (int k = 0; k < PICK_COLS; ++k) {
-        const int c = tid + PICK_THREADS * k;
-        if (c == pcol)
+          for (int i = 0; i < QRS_ROWS; ++i) x[i] = g[k][i];
+      double ss = 0.0;
 #pragma unroll
-          for (int i = 0; i < QRS_ROWS; ++i) g[k][i] = scol[1][i];
-        if (c == t)
-#pragma unroll
-          for (int i = 0; i < QRS_ROWS; ++i) g[k][i] = scol[0][i];
-      }
-    }
-    // reflector of column t (rows t ..), by its owner: thread t, slot 0
-    if (tid == t) {
-      double ss = 0.0, alpha = 0.0;
-#pragma unroll
-      for (int i = 0; i < QRS_ROWS; ++i) {
-        if (i > t) ss += g[0][i] * g[0][i];
-        if (i == t) alpha = g[0][i];
-      }
+      for (int i = 1; i < QRS_ROWS; ++i) ss += x[i] * x[i];
+      const double alpha = x[0];
       double tau = 0.0, scale = 0.0;
       if (ss > 0.0) {
         const double nrm = sqrt(alpha * alpha + ss);
@@ -1180,8 +1178,9 @@ __global__ __launch_bounds__(PICK_THREADS) void k_qr_pick(const QrTask *__restri
         tau = (beta - alpha) / beta;
         scale = 1.0 / (alpha - beta);
       }
+      sv[0] = 1.0;
 #pragma unroll
-      for (int i = 0; i < QRS_ROWS; ++i) sv[i] = i > t ? g[0][i] * scale : (i == t ? 1.0 : 0.0);
+      for (int i = 1; i < QRS_ROWS; ++i) sv[i] = x[i] * scale;
       s_tau = tau;
     }
     __syncthreads();
@@ -1189,19 +1188,28 @@ __global__ __launch_bounds__(PICK_THREADS) void k_qr_pick(const QrTask *__restri
     double v[QRS_ROWS];
 #pragma unroll
     for (int i = 0; i < QRS_ROWS; ++i) v[i] = sv[i];
+    if (tid == powner && pcol != t) {
+#pragma unroll
+      for (int k = 0; k < PICK_COLS; ++k)
+        if (pslot == k)
+#pragma unroll
+          for (int i = 0; i < QRS_ROWS; ++i) g[k][i] = scol[i];
+    }
+    // (columns up to t and past the last are updated too, and not looked at)
 #pragma unroll
     for (int k = 0; k < PICK_COLS; ++k) {
-      const int c = tid + PICK_THREADS * k;
-      if (c > t && c < nrem) {
-        double w = 0.0;
+      if (PICK_THREADS * k >= nrem) break;
+      double w = 0.0;
 #pragma unroll
-        for (int i = 0; i < QRS_ROWS; ++i) w += v[i] * g[k][i];
+      for (int i = 0; i < QRS_ROWS; ++i) w += v[i] * g[k][i];
 #pragma unroll
-        for (int i = 0; i < QRS_ROWS; ++i) g[k][i] -= tau * w * v[i];
-      }
+      for (int i = 1; i < QRS_ROWS; ++i) g[k][i - 1] = g[k][i] - tau * w * v[i];
+      g[k][QRS_ROWS - 1] = 0.0;
     }
-    __syncthreads();  // s_best, scol, sv and s_tau are rewritten next step
+    // no barrier: s_best is the other one next step, and sv, scol and s_tau
+    // are written after the next barrier
   }
+  __syncthreads();  // sswap
   // The swaps (t, sswap[t]) in sequence, applied at once: every position a
   // swap touches (t, or sswap[t]) receives the column that started at
   // src(q), found by undoing the swaps from the last; a thread moves its rows

@@ -999,16 +999,93 @@ __global__ void k_qr_rinit(const QrTask *__restrict__ tasks) {
   if (threadIdx.x == 0) *tk.rank = tk.n;
 }
 
+// Truncation test after the panel at p0 (one workgroup per task): squared
+// norms r_i of the panel's rows of R (columns i .. n - 1) and of the
+// trailing block (from the column norms k_qr_apply left in tk.work), then
+// the first k (p0 <= k <= p0 + pb, k = 0 also tested on the first panel)
+// whose tail is <= tol; *tk.rank = k when found.  Fixed summation orders, by
+// the first 256 threads; red: TAIL_LDS doubles.  It reads what the sample of
+// the next panel reads and runs beside it, as one more workgroup of its launch
+// (a launch of its own took 8.8 us of the 128 us chain of a panel).
+constexpr int TAIL_LDS = 256 + PQB * 17;
+
+__device__ __forceinline__ void qr_tail(const QrTask &tk, int p0, double *red) {
+  double(*srow)[17] = reinterpret_cast<double(*)[17]>(red + 256);
+  const int m = tk.m, n = tk.n, lda = tk.lda;
+  if (p0 >= n || *tk.rank <= p0) return;  // (no other workgroup of the launch writes it)
+  const int pb = min(PQB, n - p0), c1 = p0 + pb;
+  const int tid = threadIdx.x;
+  const double *cn = tk.work + (int64_t)QRS_ROWS * (m + n);
+  double t = 0.0;
+  // rows of R: thread (i, g) = (tid % 16, tid / 16) sums columns i + g, i + g + 16, ...
+  if (tid < 256) {
+    for (int c = c1 + tid; c < n; c += 256) t += cn[c];
+    red[tid] = t;
+    const int i = tid % PQB, g = tid / PQB;
+    double r = 0.0;
+    if (i < pb)
+      for (int c = p0 + i + g; c < n; c += 16) {
+        const double v = tk.A[(int64_t)c * lda + p0 + i];
+        r += v * v;
+      }
+    srow[i][g] = r;
+  }
+  __syncthreads();
+  for (int s = 128; s > 0; s >>= 1) {
+    if (tid < s) red[tid] += red[tid + s];
+    __syncthreads();
+  }
+  if (tid == 0) {
+    double ri[PQB];
+    for (int i = 0; i < PQB; ++i) {
+      double r = 0.0;
+      for (int g = 0; g < 16; ++g) r += srow[i][g];
+      ri[i] = r;
+    }
+    // tailsq[k - p0] = squared tail after k reflectors, k = p0 .. c1
+    double tailsq[PQB + 1];
+    double acc = red[0];
+    tailsq[pb] = acc;
+    for (int k = c1 - 1; k >= p0; --k) {
+      acc += ri[k - p0];
+      tailsq[k - p0] = acc;
+    }
+    const double tol2 = tk.tol * tk.tol;
+    int found = -1;
+    for (int k = (p0 == 0 ? p0 : p0 + 1); k <= c1 && found < 0; ++k)
+      if (tailsq[k - p0] <= tol2) found = k;
+    if (found >= 0) *tk.rank = found;
+  }
+}
+
+// (the last panel's, which no sample follows)
+__global__ __launch_bounds__(256) void k_qr_tail(const QrTask *__restrict__ tasks, int p0) {
+  __shared__ double red[TAIL_LDS];
+  qr_tail(tasks[blockIdx.x], p0, red);
+}
+
 // G[:, c] = Omega(0 : m - q0, :)^T A(q0 : m, c) for columns c >= q0, PAP_CB
-// columns per workgroup (same MFMA layout as the first product of k_qr_apply).
+// columns per workgroup (same MFMA layout as the first product of k_qr_apply),
+// and the truncation test of the panel before q0, if there is one.  The test
+// may lower the rank meanwhile: a workgroup goes by what it finds when it
+// starts, and a sample past the rank is not used.
 template <int NTH>
 __global__ __launch_bounds__(NTH) void k_qr_sample(const QrTask *__restrict__ tasks, int q0,
                                                            int nblk) {
   __shared__ double sW[NTH / 64][QRS_ROWS][PAP_CB + 1];
-  const QrTask tk = tasks[blockIdx.x / nblk];
-  const int b = blockIdx.x % nblk;
+  __shared__ int s_rank;
+  static_assert(NTH >= 256 && TAIL_LDS <= NTH / 64 * QRS_ROWS * (PAP_CB + 1), "room for the test");
+  const int per = nblk + (q0 > 0 ? 1 : 0);
+  const QrTask tk = tasks[blockIdx.x / per];
+  const int b = blockIdx.x % per;
+  if (b == nblk) {
+    qr_tail(tk, q0 - PQB, &sW[0][0][0]);
+    return;
+  }
   const int m = tk.m, n = tk.n, lda = tk.lda;
-  if (q0 >= n || *tk.rank <= q0) return;
+  if (threadIdx.x == 0) s_rank = *tk.rank;
+  __syncthreads();
+  if (q0 >= n || s_rank <= q0) return;
   const int c0 = q0 + PAP_CB * b;
   if (c0 >= n) return;
   const int M = m - q0;
@@ -1246,62 +1323,6 @@ __global__ __launch_bounds__(PICK_THREADS) void k_qr_pick(const QrTask *__restri
   if (tid < nmv) tk.piv[p0 + smove[0][tid]] = pv;
 }
 
-// Truncation test after the panel at p0 (one workgroup per task): squared
-// norms r_i of the panel's rows of R (columns i .. n - 1) and of the
-// trailing block (from the column norms k_qr_apply left in tk.work), then
-// the first k (p0 <= k <= p0 + pb, k = 0 also tested on the first panel)
-// whose tail is <= tol; *tk.rank = k when found.  Fixed summation orders.
-__global__ __launch_bounds__(256) void k_qr_tail(const QrTask *__restrict__ tasks, int p0) {
-  __shared__ double red[256];
-  __shared__ double srow[PQB][17];
-  const QrTask tk = tasks[blockIdx.x];
-  const int m = tk.m, n = tk.n, lda = tk.lda;
-  if (p0 >= n || *tk.rank <= p0) return;
-  const int pb = min(PQB, n - p0), c1 = p0 + pb;
-  const int tid = threadIdx.x;
-  const double *cn = tk.work + (int64_t)QRS_ROWS * (m + n);
-  double t = 0.0;
-  for (int c = c1 + tid; c < n; c += 256) t += cn[c];
-  red[tid] = t;
-  // rows of R: thread (i, g) = (tid % 16, tid / 16) sums columns i + g, i + g + 16, ...
-  {
-    const int i = tid % PQB, g = tid / PQB;
-    double r = 0.0;
-    if (i < pb)
-      for (int c = p0 + i + g; c < n; c += 16) {
-        const double v = tk.A[(int64_t)c * lda + p0 + i];
-        r += v * v;
-      }
-    srow[i][g] = r;
-  }
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (tid < s) red[tid] += red[tid + s];
-    __syncthreads();
-  }
-  if (tid == 0) {
-    double ri[PQB];
-    for (int i = 0; i < PQB; ++i) {
-      double r = 0.0;
-      for (int g = 0; g < 16; ++g) r += srow[i][g];
-      ri[i] = r;
-    }
-    // tailsq[k - p0] = squared tail after k reflectors, k = p0 .. c1
-    double tailsq[PQB + 1];
-    double acc = red[0];
-    tailsq[pb] = acc;
-    for (int k = c1 - 1; k >= p0; --k) {
-      acc += ri[k - p0];
-      tailsq[k - p0] = acc;
-    }
-    const double tol2 = tk.tol * tk.tol;
-    int found = -1;
-    for (int k = (p0 == 0 ? p0 : p0 + 1); k <= c1 && found < 0; ++k)
-      if (tailsq[k - p0] <= tol2) found = k;
-    if (found >= 0) *tk.rank = found;
-  }
-}
-
 __global__ void k_qr_qinit(const QrTask *__restrict__ tasks, int nblk) {
   // Q = [I; 0]: one workgroup per (task, 64 columns)
   const QrTask tk = tasks[blockIdx.x / nblk];
@@ -1403,7 +1424,7 @@ static void launch_formq(const QrTask *d_tasks, int ntask, int nmax, hipStream_t
 }
 
 static void launch_sample(const QrTask *d_tasks, int ntask, int sblk, int p0, hipStream_t st) {
-  const dim3 g(ntask * sblk);
+  const dim3 g(ntask * (sblk + (p0 > 0 ? 1 : 0)));
   switch (apply_threads()) {
     case 256: hipLaunchKernelGGL((k_qr_sample<256>), g, dim3(256), 0, st, d_tasks, p0, sblk); break;
     default: hipLaunchKernelGGL((k_qr_sample<512>), g, dim3(512), 0, st, d_tasks, p0, sblk); break;
@@ -1473,9 +1494,9 @@ int launch_qrcp_panels(const QrTask *d_tasks, int ntask, int mmax, int nmax, hip
       launch_apply<0>(d_tasks, ntask, nblk, p0, st);
       if (int rc = check_launch("qr_apply")) return rc;
     }
-    hipLaunchKernelGGL(k_qr_tail, dim3(ntask), dim3(256), 0, st, d_tasks, p0);
-    if (int rc = check_launch("qr_tail")) return rc;
   }
+  hipLaunchKernelGGL(k_qr_tail, dim3(ntask), dim3(256), 0, st, d_tasks, (nmax - 1) / PQB * PQB);
+  if (int rc = check_launch("qr_tail")) return rc;
   if (formq_fused()) {
     launch_formq(d_tasks, ntask, nmax, st);
     return check_launch("qr_formq");

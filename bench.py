@@ -470,7 +470,7 @@ def run_headline(args, mvg, dev, synthetic, torch):
 
 
 def run_batched(args, mvg, dev, synthetic, torch):
-    """Many theta on the N = 400 workload (800 x 800) in one persistent launch."""
+    """Many theta on the N = 400 workload (800 x 800) in one batch."""
     n = 400
     th0 = synthetic.THETA_REF
     xr, yr = synthetic.jittered_grid(n, args.seed)
@@ -506,7 +506,7 @@ def run_batched(args, mvg, dev, synthetic, torch):
     _line(METRIC,
           args.batch / dt, "evals/s", args.steps, warm, 1e3 * dt, "f64",
           {"workload": "batched FP64 loglik, %d theta (+-20%% around (1,1,0.1,0.5,1,0.5)) on "
-                       "N=%d locations (%dx%d), one persistent launch" % (args.batch, n, 2 * n, 2 * n),
+                       "N=%d locations (%dx%d), one batch" % (args.batch, n, 2 * n, 2 * n),
            "n_loc": n, "batch": args.batch, "precision": "fp64"},
           single_call_evals_per_s=single, speedup_vs_single_calls=(args.batch / dt) / single,
           simplex7_ms=1e3 * (time.perf_counter() - t2), failed=int((r["status"] != 0).sum()))

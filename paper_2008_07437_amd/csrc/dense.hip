@@ -629,8 +629,8 @@ __global__ void k_copy_panel(TileMap M, int k, double *__restrict__ P) {
 }
 
 // SYRK of one diagonal tile, A_jj -= L_jk L_jk^T (lower 64-blocks), with the
-// small-footprint 64 x 64 block GEMM so that it runs next to the persistent
-// trailing update instead of waiting for it to drain.
+// small-footprint 64 x 64 block GEMM so that it runs next to the trailing
+// update instead of waiting for it to drain.
 __global__ __launch_bounds__(256) void k_syrk64(TileMap M, int k, int j) {
   __shared__ double smem[SMALL_LDS];
   const int s = M.nb / PB;

@@ -59,7 +59,8 @@ def test_factor_block_edges(lib, orc, n, nb):
     np.testing.assert_allclose(S @ w, z, rtol=0, atol=1e-9 * np.max(np.abs(z)))
 
 
-# the tiled path, its last steps and the 64-wide tail on both sides of the switch
+# around 6,144 rows at every larger tile size: 64-wide steps throughout (tile
+# steps, from 8,194 rows on, are in test_gpu_tiled.py)
 @pytest.mark.parametrize("n,nb", [(3071, 128), (3072, 256), (3073, 512), (3100, 768), (3600, 1024)])
 def test_tiled_and_tail(lib, n, nb):
     print("tiled n=%d nb=%d" % (n, nb), flush=True)

@@ -269,10 +269,15 @@ __global__ void k_reduce_chunks(const double *__restrict__ part, int64_t m, int 
                                 double *__restrict__ zhat) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // i = 2t + j
   if (i >= 2 * m) return;
-  const int64_t t = i / 2;
-  const int j = (int)(i % 2);
   double s = 0.0;
-  for (int c = 0; c < nchunk; ++c) s += part[(t * nchunk + c) * 2 + j];
+  for (int c = 0; c < nchunk; c += 8) {  // eight loads in flight
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)min(c + u, nchunk - 1) * 2 * m + i];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += c + u < nchunk ? v[u] : 0.0;
+  }
   zhat[i] = s;
 }
 
@@ -1657,7 +1662,7 @@ int cokrige_predict(const mvg_factor *F, const double *d_x0, const double *d_y0,
   if (!d_zhat) return -5;
   hipStream_t st = (hipStream_t)hip_stream;
   const mvg_mat *A = F->A;
-  const int span = cokrige_chunk(A->n_loc, m);
+  const int span = cokrige_span(A->n_loc);
   const int nchunk = (int)((A->n_loc + span - 1) / span);
   int hc = prof_begin(MVG_PROF_COKRIGE, st, 0.0, 8.0 * (double)A->N);
   double *part = nullptr;

@@ -335,66 +335,91 @@ int launch_cov_tiles_p(const MaternArgsP &P, const double *d_qtab, const double 
 
 // ---------------------------------------------------------------- cokriging
 
-// Locations per workgroup: up to 2048, fewer where that leaves less than about
-// 1024 workgroups (100 targets on 5,000 locations: 512 a workgroup instead of
-// 2048, one target's sum was the length of the launch).
-int cokrige_chunk(int64_t n_loc, int64_t m) {
-  const int64_t c = (n_loc * m / 1024 + 255) / 256 * 256;
-  return (int)std::min<int64_t>(2048, std::max<int64_t>(256, c));
+// Locations per partial sum: 256, more only where that makes over 64 sums a
+// target.  From n_loc alone: how many targets share a call may not change the
+// order of a target's sum.
+int cokrige_span(int64_t n_loc) {
+  return 256 * (int)((n_loc + 256 * 64 - 1) / (256 * 64));
 }
 
-// part[(t * nchunk + chunk) * 2 + j] = sum over the chunk's locations r and
-// i in {0,1} of C_ij(||s0_t - s_r||) w[2r+i].
+// v summed over the 16 lanes of a row (DPP row_ror), in every lane
+template <int N>
+__device__ __forceinline__ double row_ror(double v) {
+  return __longlong_as_double(
+      __builtin_amdgcn_update_dpp(0L, (long)__double_as_longlong(v), 0x120 + N, 0xF, 0xF, true));
+}
+__device__ __forceinline__ double row_sum(double v) {
+  v += row_ror<8>(v);
+  v += row_ror<4>(v);
+  v += row_ror<2>(v);
+  return v + row_ror<1>(v);
+}
+
+constexpr int COK_TARGETS = 16;  // targets of a workgroup at most
+
+// part[chunk 2m + 2t + j] = sum over the chunk's locations r and i in {0,1} of
+// C_ij(||s0_t - s_r||) w[2r+i].  A workgroup takes one chunk and tg targets one
+// after another, its table and its locations held; the sums do not depend on tg.
+// Bound by the pairs' polynomials (LDS reads).  Whole predictions of 100 and
+// 4,000 targets on 5,000 locations take 41 and 146 us; with one target and a
+// chunk of 256 to 2,048 locations a workgroup, chosen from both counts, 45 and 169.
 template <int FORM>
 __global__ __launch_bounds__(256) void k_cokrige_dot(MaternArgs P, const double *__restrict__ qtab,
                                                      const double *__restrict__ xs,
                                                      const double *__restrict__ ys, int64_t n_loc,
                                                      const double *__restrict__ x0,
-                                                     const double *__restrict__ y0,
+                                                     const double *__restrict__ y0, int64_t m,
                                                      const double *__restrict__ w,
-                                                     double *__restrict__ part, int nchunk,
-                                                     int span) {
+                                                     double *__restrict__ part, int nchunk, int span,
+                                                     int tg) {
   __shared__ double ct[cov_lds(FORM)];
-  __shared__ double red[2][256];
+  __shared__ double red[COK_TARGETS][2][16];
   load_cov_table<FORM>(qtab, ct);
-  const int64_t t = blockIdx.x / nchunk;
-  const int chunk = blockIdx.x % nchunk;
-  const double xt = x0[t], yt = y0[t];
-  double a0 = 0.0, a1 = 0.0;
-  const int64_t r0 = (int64_t)chunk * span;
-  for (int q = threadIdx.x; q < span; q += 256) {
-    const int64_t r = r0 + q;
-    if (r >= n_loc) break;
-    double c[3];
-    cross_cov_block<FORM>(xt, yt, xs[r], ys[r], P, ct, qtab, c);
-    const double w0 = w[2 * r], w1 = w[2 * r + 1];
-    a0 += c[0] * w0 + c[2] * w1;  // Zhat_1 += C11 w_1 + C21 w_2
-    a1 += c[2] * w0 + c[1] * w1;  // Zhat_2 += C12 w_1 + C22 w_2
-  }
-  red[0][threadIdx.x] = a0;
-  red[1][threadIdx.x] = a1;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      red[0][threadIdx.x] += red[0][threadIdx.x + s];
-      red[1][threadIdx.x] += red[1][threadIdx.x + s];
+  const int tid = threadIdx.x, chunk = blockIdx.x % nchunk;
+  const int64_t t0 = (int64_t)(blockIdx.x / nchunk) * tg;
+  const int nt = (int)min((int64_t)tg, m - t0);
+  const int64_t r0 = (int64_t)chunk * span + tid, r1 = min(n_loc, (int64_t)(chunk + 1) * span);
+  const int64_t rc = min(r0, n_loc - 1);
+  const double xr = xs[rc], yr = ys[rc], w0 = w[2 * rc], w1 = w[2 * rc + 1];
+  for (int t = 0; t < nt; ++t) {
+    const double xt = x0[t0 + t], yt = y0[t0 + t];
+    double a0 = 0.0, a1 = 0.0, c[3];
+    if (r0 < r1) {
+      cross_cov_block<FORM>(xt, yt, xr, yr, P, ct, qtab, c);
+      a0 = c[0] * w0 + c[2] * w1;  // Zhat_1 += C11 w_1 + C21 w_2
+      a1 = c[2] * w0 + c[1] * w1;  // Zhat_2 += C12 w_1 + C22 w_2
     }
-    __syncthreads();
+    for (int64_t r = r0 + 256; r < r1; r += 256) {
+      cross_cov_block<FORM>(xt, yt, xs[r], ys[r], P, ct, qtab, c);
+      a0 += c[0] * w[2 * r] + c[2] * w[2 * r + 1];
+      a1 += c[2] * w[2 * r] + c[1] * w[2 * r + 1];
+    }
+    a0 = row_sum(a0);
+    a1 = row_sum(a1);
+    if ((tid & 15) == 0) {
+      red[t][0][tid >> 4] = a0;
+      red[t][1][tid >> 4] = a1;
+    }
   }
-  if (threadIdx.x == 0) {
-    part[(t * nchunk + chunk) * 2 + 0] = red[0][0];
-    part[(t * nchunk + chunk) * 2 + 1] = red[1][0];
+  __syncthreads();
+  if (tid < 2 * nt) {
+    double s = 0.0;
+#pragma unroll
+    for (int g = 0; g < 16; ++g) s += red[tid >> 1][tid & 1][g];
+    part[(int64_t)chunk * 2 * m + 2 * t0 + tid] = s;
   }
 }
 
 int launch_cokrige_dot(const MaternArgs &P, const double *d_qtab, const double *d_x,
                        const double *d_y, int64_t n_loc, const double *d_x0, const double *d_y0,
                        int64_t m, const double *d_w, double *d_part, int nchunk, hipStream_t st) {
-  const dim3 grid((unsigned)(m * nchunk));
-  const int span = cokrige_chunk(n_loc, m);
+  // about 1,024 workgroups (four to a CU)
+  const int tg = (int)std::min<int64_t>(COK_TARGETS, (m * nchunk + 1023) / 1024);
+  const dim3 grid((unsigned)((m + tg - 1) / tg * nchunk));
+  const int span = cokrige_span(n_loc);
 #define MVG_FORM(F)                                                                              \
   hipLaunchKernelGGL(k_cokrige_dot<F>, grid, dim3(256), 0, st, P, d_qtab, d_x, d_y, n_loc, d_x0, \
-                     d_y0, d_w, d_part, nchunk, span)
+                     d_y0, m, d_w, d_part, nchunk, span, tg)
   switch (cov_form(P)) {
     case COV_TABLE: MVG_FORM(COV_TABLE); break;
     case COV_QUAD: MVG_FORM(COV_QUAD); break;

@@ -167,7 +167,7 @@ int launch_cov_tiles(const MaternArgs &P, const double *d_qtab, const double *d_
 // p-variate Sigma (p != 2 or on request) over all tiles of M
 int launch_cov_tiles_p(const MaternArgsP &P, const double *d_qtab, const double *d_x,
                        const double *d_y, int64_t n_loc, TileMap M, hipStream_t st);
-int cokrige_chunk(int64_t n_loc, int64_t m);  // locations per partial sum of cokrige_dot
+int cokrige_span(int64_t n_loc);  // locations per partial sum of cokrige_dot
 // c0^T w and optionally ||L^-1 c0||^2 pieces for cokriging
 int launch_cokrige_dot(const MaternArgs &P, const double *d_qtab, const double *d_x,
                        const double *d_y, int64_t n_loc, const double *d_x0, const double *d_y0,

@@ -1,0 +1,58 @@
+"""What a prediction may depend on: the factor and its own target, not how many
+targets share the call."""
+import numpy as np
+import pytest
+
+import synthetic
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a HIP device")
+    import paper_2008_07437_amd as m
+    m._lib._load()
+    return m
+
+
+def _dev(a):
+    import torch
+    return torch.as_tensor(np.ascontiguousarray(a, dtype=np.float64)).cuda()
+
+
+def _factor(lib, orc, n, nb, th):
+    x, y = synthetic.jittered_grid(n, 8)
+    p = orc.morton_order(x, y)
+    x, y, z = x[p], y[p], synthetic.normal_eps(2 * n, 8)
+    _, F = lib.loglik(_dev(x), _dev(y), _dev(z), th, {"nb": nb}, keep=True)
+    return x, y, F, F.w(n).cpu().numpy()
+
+
+# locations at the edges of a partial sum (256 of them) and past 64 sums, every
+# form of the covariance (closed orders, the quadrature below 128 locations, the
+# polynomials), and targets from one to several times what a workgroup takes
+@pytest.mark.parametrize("n,nb,nu", [(1, 128, (0.5, 1.0)), (100, 128, (0.7, 1.1)), (255, 128, (0.5, 1.5)),
+                                     (256, 256, (0.5, 1.0)), (257, 256, (0.7, 1.1)), (1000, 256, (0.5, 1.0)),
+                                     (5000, 512, (0.5, 1.0)), (16400, 1024, (0.5, 1.0))])
+def test_alone_equals_in_a_map(lib, orc, n, nb, nu):
+    print("alone = in a map: n=%d" % n, flush=True)
+    th = (1.2, 0.8, 0.1, nu[0], nu[1], 0.4)
+    x, y, F, w = _factor(lib, orc, n, nb, th)
+    m = 3001
+    x0, y0 = (_dev(v) for v in synthetic.uniform_targets(m, 8))
+    got = lib.cokrige_predict(F, x0, y0).cpu().numpy()
+    for lo, hi in ((0, 1), (1, 2), (m - 1, m), (7, 24), (100, 133), (500, 1600)):
+        part = lib.cokrige_predict(F, x0[lo:hi].contiguous(), y0[lo:hi].contiguous()).cpu().numpy()
+        assert np.array_equal(part, got[lo:hi]), (lo, hi)
+    at = np.array([0, 15, 16, 17, 1500, m - 1])
+    c0 = orc.cross_cov_targets(x, y, x0.cpu().numpy()[at], y0.cpu().numpy()[at], th)
+    # 2n products, each and their sums rounded: 2n + 8 roundings of 2^-53, and
+    # covariances within 1e-13 relative
+    for k, t in enumerate(at):
+        for j in range(2):
+            terms = c0[:, 2 * k + j] * w
+            tol = (1e-13 + (2 * n + 8) * 2.0 ** -53) * np.abs(terms).sum()
+            assert abs(got[t, j] - terms.sum()) <= tol, (t, j)

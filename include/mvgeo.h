@@ -366,7 +366,11 @@ int tlr_compress(const double *d_x, const double *d_y, int64_t n_loc,
  *   Zhat(s0) = c0^T Sigma^-1 Z,  c0[2r+i, j] = C_ij(||s0 - s_r||).
  * d_x0, d_y0: m targets (device).  d_zhat: 2m FP64, (Zhat_1, Zhat_2) per
  * target.  d_mse (nullable): m FP64 predictor MSE tr{C(0) - c0^T Sigma^-1 c0}
- * (Eq. 5).  Returns 0, -1..-7, MVG_ERR_*. */
+ * (Eq. 5).  A target's Zhat does not depend on the other targets of the call
+ * (bitwise).  Its MSE may differ in the last bits between a call for one
+ * target, one for 2 to 79 and one for 80 and more, which solve in other orders;
+ * within these it does not depend on them on an FP64 factor.
+ * Returns 0, -1..-7, MVG_ERR_*. */
 int cokrige_predict(const mvg_factor *F, const double *d_x0, const double *d_y0,
                     int64_t m, double *d_zhat, double *d_mse, void *hip_stream);
 

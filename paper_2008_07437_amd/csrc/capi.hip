@@ -1649,8 +1649,8 @@ int mloe_mmom(const double *d_x, const double *d_y, int64_t n_loc, const mvg_the
 
 // From this many targets on the errors' solve takes the right-hand sides
 // transposed on the trailing update's kernel (padded to 128 of them); below,
-// or where its memory is short, the task-list products (1000 targets on 5,000
-// locations 6.1 -> 4.9 ms; 64 on 1,000 at nb = 256 539 us there, 549 here).
+// the task-list products (1000 targets on 5,000 locations 6.1 -> 4.9 ms; 64 on
+// 1,000 at nb = 256 539 us there, 546 here; 2 on 9,000 4.46 ms there, 5.05 here).
 constexpr int64_t MSE_RHS_MIN = 80;
 
 int cokrige_predict(const mvg_factor *F, const double *d_x0, const double *d_y0, int64_t m,
@@ -1680,22 +1680,35 @@ int cokrige_predict(const mvg_factor *F, const double *d_x0, const double *d_y0,
   }
   hipFreeAsync(part, st);
   prof_end(hc, st);
-  const int ld = (int)((2 * m + 127) / 128 * 128);
-  double *VY = nullptr;  // V and Y, then the sums of squares by chunks
-  const int64_t nsq = (A->Np + RHS_CHUNK - 1) / RHS_CHUNK;
-  if (!rc && d_mse && A->precision == MVG_FP64 && m >= MSE_RHS_MIN &&
-      malloc_async((void **)&VY, sizeof(double) * (2 * A->Np + nsq) * ld, st) == hipSuccess) {
-    double *V = VY, *Y = V + A->Np * ld, *sq = Y + A->Np * ld;
-    rc = launch_cokrige_c0t(A->margs, A->d_qtab, A->d_x, A->d_y, A->n_loc, A->Np, d_x0, d_y0, m, ld,
-                            V, st);
-    if (!rc) rc = trsm_forward_rhs(A, V, Y, ld, sq, st);
-    if (!rc) {
-      hipLaunchKernelGGL(k_mse_chunks, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, st,
-                         (const double *)sq, m, nsq, ld, A->theta.sigma11_sq + A->theta.sigma22_sq,
-                         d_mse);
-      rc = check_launch("mse_chunks");
+  if (!rc && d_mse && A->precision == MVG_FP64 && m >= MSE_RHS_MIN) {
+    // every target at once, or where memory is short in groups, down to 64 (less
+    // than the other path needs): a target's sums are the same in any group
+    const int64_t nsq = (A->Np + RHS_CHUNK - 1) / RHS_CHUNK;
+    int64_t group = (m + 63) / 64 * 64;
+    double *V = nullptr;  // V and Y, then the sums of squares by chunks
+    while (malloc_async((void **)&V, sizeof(double) * (2 * A->Np + nsq) * 2 * group, st) !=
+           hipSuccess) {
+      if (group == 64) {
+        set_error("workspace allocation failed");
+        return MVG_ERR_ALLOC;
+      }
+      group = (group / 2 + 63) / 64 * 64;
     }
-    hipFreeAsync(VY, st);
+    for (int64_t t0 = 0; t0 < m && !rc; t0 += group) {
+      const int64_t mg = std::min(group, m - t0);
+      const int ld = (int)((2 * mg + 127) / 128 * 128);
+      double *Y = V + A->Np * ld, *sq = Y + A->Np * ld;
+      rc = launch_cokrige_c0t(A->margs, A->d_qtab, A->d_x, A->d_y, A->n_loc, A->Np, d_x0 + t0,
+                              d_y0 + t0, mg, ld, V, st);
+      if (!rc) rc = trsm_forward_rhs(A, V, Y, ld, sq, st);
+      if (!rc) {
+        hipLaunchKernelGGL(k_mse_chunks, dim3((unsigned)((mg + 255) / 256)), dim3(256), 0, st,
+                           (const double *)sq, mg, nsq, ld,
+                           A->theta.sigma11_sq + A->theta.sigma22_sq, d_mse + t0);
+        rc = check_launch("mse_chunks");
+      }
+    }
+    hipFreeAsync(V, st);
   } else if (!rc && d_mse) {
     double *V = nullptr, *ss = nullptr;
     if (malloc_async((void **)&V, sizeof(double) * (A->Np * 2 * m + 2 * m), st) != hipSuccess) {

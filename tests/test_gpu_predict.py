@@ -56,3 +56,23 @@ def test_alone_equals_in_a_map(lib, orc, n, nb, nu):
             terms = c0[:, 2 * k + j] * w
             tol = (1e-13 + (2 * n + 8) * 2.0 ** -53) * np.abs(terms).sum()
             assert abs(got[t, j] - terms.sum()) <= tol, (t, j)
+
+
+# the errors' three solves: one target, 2 to 79, 80 and more
+@pytest.mark.parametrize("n,nb", [(40, 128), (300, 128), (1000, 256), (1500, 512), (1100, 1024)])
+def test_errors_alone_equal_in_a_map(lib, orc, n, nb):
+    print("errors alone = in a map: n=%d nb=%d" % (n, nb), flush=True)
+    _, _, F, _ = _factor(lib, orc, n, nb, synthetic.THETA_REF)
+    x0, y0 = (_dev(v) for v in synthetic.uniform_targets(700, 8))
+
+    def call(lo, hi):
+        return lib.cokrige_predict(F, x0[lo:hi].contiguous(), y0[lo:hi].contiguous(), with_mse=True)[1].cpu().numpy()
+    got = call(0, 700)
+    for lo, hi in ((0, 80), (63, 191), (100, 301), (619, 700)):
+        assert np.array_equal(call(lo, hi), got[lo:hi]), (lo, hi)
+    few = call(0, 79)
+    for lo, hi in ((0, 2), (3, 20), (30, 64)):
+        assert np.array_equal(call(lo, hi), few[lo:hi]), (lo, hi)
+    # the solves agree to the tolerance of the errors against the oracle
+    np.testing.assert_allclose(few, got[:79], rtol=1e-8, atol=1e-12)
+    np.testing.assert_allclose(call(5, 6), got[5:6], rtol=1e-8, atol=1e-12)

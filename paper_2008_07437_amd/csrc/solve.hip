@@ -459,17 +459,20 @@ int launch_dot_cols(const double *d_A, const double *d_B, int64_t Np, int ncols,
 }
 
 // z = L eps: 32 rows by up to TRMV_COLS columns (whole tiles) per workgroup,
-// part[chunk][row], then the chunks added in order.  The diagonal tile's upper
-// part is scratch and not used.  Bound by the factor's bytes; one thread per
-// row before: 1.5 ms at 2n = 6,400, now 0.05.
-constexpr int TRMV_COLS = 1024;
+// part[chunk][row], then the chunks added in order, TRMV_CHUNKS at a time: the
+// workspace is at most that many vectors (all 47 of 48,000 rows at once: 1.59
+// ms, 32: 1.60; 16 cost 4 % at 18,000), and the sums are the same for any
+// number.  The diagonal tile's upper part is scratch and not used.  Bound by the
+// factor's bytes; one thread per row before: 1.5 ms at 2n = 6,400, now 0.03.
+constexpr int TRMV_COLS = 1024, TRMV_CHUNKS = 32;
 
+// (chunks from c0 on; row tiles from the first that they reach)
 __global__ __launch_bounds__(256) void k_trmv_part(TileMap M, const double *__restrict__ eps,
-                                                   double *__restrict__ out, int64_t Np) {
+                                                   double *__restrict__ out, int64_t Np, int c0) {
   __shared__ double x[1024], part[16][SR];
   const int nb = M.nb, chunks = nb / SR, per = max(1, TRMV_COLS / nb);
-  const int I = blockIdx.x / chunks, r0 = (blockIdx.x % chunks) * SR;
-  const int J0 = blockIdx.y * per, J1 = min(I + 1, J0 + per);
+  const int I = c0 * per + blockIdx.x / chunks, r0 = (blockIdx.x % chunks) * SR;
+  const int J0 = (c0 + blockIdx.y) * per, J1 = min(I + 1, J0 + per);
   if (J0 > I) return;
   const int p = threadIdx.x & 15, g = threadIdx.x >> 4;
   double s = 0.0;
@@ -502,32 +505,38 @@ __global__ __launch_bounds__(256) void k_trmv_part(TileMap M, const double *__re
     out[(int64_t)blockIdx.y * Np + (int64_t)I * nb + r0 + threadIdx.x] = s;
 }
 
-__global__ void k_trmv_sum(const double *__restrict__ part, int64_t Np, int nb, int64_t N,
-                           double *__restrict__ z) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// the rows of tile rows c0 per .. on: chunks c0 .. c0 + nc - 1 added to z
+__global__ void k_trmv_sum(const double *__restrict__ part, int64_t Np, int nb, int64_t N, int c0,
+                           int nc, double *__restrict__ z) {
+  const int per = max(1, TRMV_COLS / nb);
+  const int64_t g = (int64_t)c0 * per * nb + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= N) return;
-  const int n = (int)(g / nb) / max(1, TRMV_COLS / nb) + 1;
-  double s = 0.0;
+  const int n = min(nc, (int)(g / nb) / per + 1 - c0);
+  double s = c0 > 0 ? z[g] : 0.0;
   for (int c = 0; c < n; ++c) s += part[c * Np + g];
   z[g] = s;
 }
 
 int launch_trmv(const mvg_mat *A, const double *d_eps, double *d_z, hipStream_t st) {
   // eps is read up to the padded length: a zero-padded copy, then the parts
-  const int per = std::max(1, TRMV_COLS / A->nb), chunks = (A->T + per - 1) / per;
+  const int nb = A->nb, per = std::max(1, TRMV_COLS / nb), chunks = (A->T + per - 1) / per;
   double *ep = nullptr;
-  if (malloc_async((void **)&ep, sizeof(double) * A->Np * (1 + chunks), st) != hipSuccess) {
+  if (malloc_async((void **)&ep, sizeof(double) * A->Np * (1 + std::min(chunks, TRMV_CHUNKS)), st) !=
+      hipSuccess) {
     hipGetLastError();
     set_error("trmv workspace allocation failed");
     return MVG_ERR_ALLOC;
   }
+  double *part = ep + A->Np;
   int rc = launch_fill_f64(ep, 0.0, A->Np, st);
-  if (!rc) {
-    hipMemcpyAsync(ep, d_eps, sizeof(double) * A->N, hipMemcpyDeviceToDevice, st);
-    hipLaunchKernelGGL(k_trmv_part, dim3(A->T * (A->nb / SR), chunks), dim3(256), 0, st, A->map(),
-                       (const double *)ep, ep + A->Np, A->Np);
-    hipLaunchKernelGGL(k_trmv_sum, dim3((unsigned)((A->N + 255) / 256)), dim3(256), 0, st,
-                       (const double *)(ep + A->Np), A->Np, A->nb, A->N, d_z);
+  if (!rc) hipMemcpyAsync(ep, d_eps, sizeof(double) * A->N, hipMemcpyDeviceToDevice, st);
+  for (int c0 = 0; c0 < chunks && !rc; c0 += TRMV_CHUNKS) {
+    const int nc = std::min(TRMV_CHUNKS, chunks - c0);
+    hipLaunchKernelGGL(k_trmv_part, dim3((A->T - c0 * per) * (nb / SR), nc), dim3(256), 0, st,
+                       A->map(), (const double *)ep, part, A->Np, c0);
+    const int64_t rows = A->N - (int64_t)c0 * per * nb;
+    hipLaunchKernelGGL(k_trmv_sum, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st,
+                       (const double *)part, A->Np, nb, A->N, c0, nc, d_z);
     rc = check_launch("trmv");
   }
   hipFreeAsync(ep, st);

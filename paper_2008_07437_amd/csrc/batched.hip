@@ -38,12 +38,13 @@ constexpr int SMALL_GROUP = 1024;  // tasks that advance together at most
 
 __host__ __device__ inline int small_blocks(int64_t n) { return (int)((2 * n + CB - 1) / CB); }
 
-// One task's workspace: lower 64 x 64 blocks of the matrix (column-major
+// One task's workspace, sized by its own n (at SmallTask::ws): lower 64 x 64 blocks of the matrix (column-major
 // inside, rows of blocks one after another), inverses of the diagonal blocks,
 // right-hand side, solution, quadrature table, pivot info.
 struct SmallSlot {
   double *base;
   int nk;
+  __device__ SmallSlot(double *ws, const SmallTask &t) : base(ws + t.ws), nk(small_blocks(t.n)) {}
   __device__ double *blk(int R, int C) const { return base + (int64_t)(R * (R + 1) / 2 + C) * CB * CB; }
   __device__ double *inv(int k) const {
     return base + (int64_t)(nk * (nk + 1) / 2 + k) * CB * CB;
@@ -54,12 +55,25 @@ struct SmallSlot {
   __device__ int64_t *info() const { return reinterpret_cast<int64_t *>(qtab() + QTAB); }
 };
 
-size_t small_workspace_doubles(int64_t nmax) {
-  const size_t k = small_blocks(nmax);
+size_t small_workspace_doubles(int64_t n) {
+  const size_t k = small_blocks(n);
   return (k * (k + 1) / 2 + k) * CB * CB + 2 * CB * k + QTAB + 32;
 }
 
-int small_batch_slots(int ntask) { return std::min(ntask, SMALL_GROUP); }
+size_t small_layout(SmallTask *tasks, int ntask, size_t limit) {
+  size_t most = 0, used = 0;
+  for (int i = 0, first = 0; i < ntask; ++i) {
+    const size_t w = small_workspace_doubles(tasks[i].n);
+    if (i > first && (used + w > limit || i - first == SMALL_GROUP)) {
+      first = i;
+      used = 0;
+    }
+    tasks[i].ws = (int64_t)used;
+    used += w;
+    most = std::max(most, used);
+  }
+  return most;
+}
 
 // Workgroup index b of a list of ntask x per workgroups, the tasks dealt to
 // the XCDs (workgroups go to them round robin), so that a task's workgroups
@@ -72,10 +86,10 @@ __device__ __forceinline__ bool task_of(int b, int ntask, int per, int &task, in
 }
 
 __global__ __launch_bounds__(256) void k_small_prep(const SmallTask *__restrict__ tasks, double *ws,
-                                                    int64_t stride, int groups) {
+                                                    int groups) {
   const int task = blockIdx.x / groups, grp = blockIdx.x % groups;
   const SmallTask &tk = tasks[task];
-  const SmallSlot s{ws + (int64_t)task * stride, small_blocks(tk.n)};
+  const SmallSlot s(ws, tk);
   if (grp > 0 && !tk.P.table) return;
   theta_tables(grp, tk.P, s.qtab());
   if (grp > 0) return;
@@ -124,12 +138,12 @@ __device__ __forceinline__ void small_pairs(const SmallTask &tk, const SmallSlot
 }
 
 __global__ __launch_bounds__(256) void k_small_cov(const SmallTask *__restrict__ tasks, int ntask,
-                                                   double *ws, int64_t stride, int per) {
+                                                   double *ws, int per) {
   __shared__ double ct[CT_SIZE];
   int task, item;
   if (!task_of(blockIdx.x, ntask, per, task, item)) return;
   const SmallTask &tk = tasks[task];
-  const SmallSlot s{ws + (int64_t)task * stride, small_blocks(tk.n)};
+  const SmallSlot s(ws, tk);
   if (item >= small_cov_items(tk.n, tk.P.table)) return;
   if (!tk.P.table) {
     if (tk.P.any_quad) small_pairs<COV_QUAD>(tk, s, item, ct);
@@ -222,13 +236,13 @@ __device__ __forceinline__ void small_finish(const SmallSlot &s, int n, double *
 // Step t of every task: first each task's row t + 1 (the serial chain) or, at
 // its end, its sums; then the other rows and the two blocks ahead.
 __global__ __launch_bounds__(256, 2) void k_small_step(const SmallTask *__restrict__ tasks, int ntask,
-                                                       double *ws, int64_t stride, int t, int per,
+                                                       double *ws, int t, int per,
                                                        double *__restrict__ out) {
   __shared__ double sm[CHOL_LDS];
   int b = blockIdx.x;
   if (b < ntask) {
     const SmallTask &tk = tasks[b];
-    const SmallSlot s{ws + (int64_t)b * stride, small_blocks(tk.n)};
+    const SmallSlot s(ws, tk);
     if (t + 1 < s.nk) {
       RowStep r{};
       r.ld = r.ldw = CB;
@@ -258,7 +272,7 @@ __global__ __launch_bounds__(256, 2) void k_small_step(const SmallTask *__restri
   }
   int task, item;
   if (!task_of(b - ntask, ntask, per, task, item)) return;
-  const SmallSlot s{ws + (int64_t)task * stride, small_blocks(tasks[task].n)};
+  const SmallSlot s(ws, tasks[task]);
   if (item < 2) {  // ahead: (t + 2, t + 1), (t + 2, t + 2)
     const int R = t + 2, C = t + 1 + item;
     if (R >= s.nk || t < 1) return;
@@ -285,16 +299,11 @@ __global__ __launch_bounds__(256, 2) void k_small_step(const SmallTask *__restri
   solve_rows(x, part, part + 16 * CT + (threadIdx.x >> 6) * CB, s.v() + CB * R);
 }
 
-int launch_small_loglik(const SmallTask *d_tasks, const SmallTask *h_tasks, int ntask, int64_t nmax,
-                        double *d_ws, int slots, double *d_out, hipStream_t st) {
-  if (ntask <= 0) return 0;
-  if (2 * nmax > SMALL_MAX || slots < 1) {
-    set_error("batched small likelihood: 2n = %lld above %d", (long long)(2 * nmax), SMALL_MAX);
-    return MVG_ERR_LIMIT;
-  }
-  const int64_t stride = (int64_t)small_workspace_doubles(nmax);
-  for (int g = 0; g < ntask; g += slots) {
-    const int cnt = std::min(slots, ntask - g), cnt8 = (cnt + 7) / 8 * 8;
+int launch_small_loglik(const SmallTask *d_tasks, const SmallTask *h_tasks, int ntask, double *d_ws,
+                        double *d_out, hipStream_t st) {
+  for (int g = 0, cnt = 0; g < ntask; g += cnt) {
+    for (cnt = 1; g + cnt < ntask && h_tasks[g + cnt].ws > 0;) ++cnt;
+    const int cnt8 = (cnt + 7) / 8 * 8;
     const SmallTask *tk = d_tasks + g;
     int64_t big = 1;
     int per = 1, tables = 0;
@@ -304,16 +313,19 @@ int launch_small_loglik(const SmallTask *d_tasks, const SmallTask *h_tasks, int 
       per = std::max(per, small_cov_items(t.n, t.P.table));
       tables |= t.P.table;
     }
+    if (2 * big > SMALL_MAX) {
+      set_error("batched small likelihood: 2n = %lld above %d", (long long)(2 * big), SMALL_MAX);
+      return MVG_ERR_LIMIT;
+    }
     const int nk = small_blocks(big), groups = tables ? (CT_HI - CT_LO) / CT_GROUP : 1;
-    hipLaunchKernelGGL(k_small_prep, dim3(cnt * groups), dim3(256), 0, st, tk, d_ws, stride,
-                       groups);
-    hipLaunchKernelGGL(k_small_cov, dim3(cnt8 * per), dim3(256), 0, st, tk, cnt, d_ws, stride, per);
+    hipLaunchKernelGGL(k_small_prep, dim3(cnt * groups), dim3(256), 0, st, tk, d_ws, groups);
+    hipLaunchKernelGGL(k_small_cov, dim3(cnt8 * per), dim3(256), 0, st, tk, cnt, d_ws, per);
     if (int rc = check_launch("small_cov")) return rc;
     for (int t = -1; t < nk; ++t) {
       const int rows = t < 0 ? 0 : std::max(0, nk - (t + 2));  // rows R >= t + 2
       const int p = rows ? rows + 2 : 0;
-      hipLaunchKernelGGL(k_small_step, dim3(cnt + cnt8 * p), dim3(256), 0, st, tk, cnt, d_ws, stride,
-                         t, std::max(1, p), d_out + 4 * (int64_t)g);
+      hipLaunchKernelGGL(k_small_step, dim3(cnt + cnt8 * p), dim3(256), 0, st, tk, cnt, d_ws, t,
+                         std::max(1, p), d_out + 4 * (int64_t)g);
       if (int rc = check_launch("small_step")) return rc;
     }
   }

@@ -249,16 +249,20 @@ struct SmallTask {
   int64_t n;
   MaternArgs P;
   double t0, t1;            // pivot tolerances (2^-40 sigma_ii^2)
+  int64_t ws;               // where its workspace begins (doubles); 0 begins a group
 };
-// out: 4 per task; d_ws holds `slots` workspaces of small_workspace_doubles(nmax),
-// at most that many tasks advance together.  d_tasks: the device copy of h_tasks
-int launch_small_loglik(const SmallTask *d_tasks, const SmallTask *h_tasks, int ntask, int64_t nmax,
-                        double *d_ws, int slots, double *d_out, hipStream_t st);
+// Gives the tasks their workspaces one after another.  A task with which they
+// would be over `limit` doubles, or too many, begins a group that uses the memory
+// anew.  Returns the doubles of the largest group (above limit only where one
+// task alone is).
+size_t small_layout(SmallTask *tasks, int ntask, size_t limit);
+size_t small_workspace_doubles(int64_t n);  // one task's
+// d_tasks: the device copy of h_tasks, laid out in d_ws; out: 4 per task
+int launch_small_loglik(const SmallTask *d_tasks, const SmallTask *h_tasks, int ntask, double *d_ws,
+                        double *d_out, hipStream_t st);
 // a task of the batched kernel from a dataset and theta (theta validated by the caller)
 SmallTask small_task(const double *x, const double *y, const double *z, int64_t n,
                      const mvg_theta &th);
-size_t small_workspace_doubles(int64_t nmax);
-int small_batch_slots(int ntask);  // workspaces worth holding for ntask tasks
 
 // second stream of the calling thread for look-ahead (default priority)
 hipStream_t side_stream();

@@ -13,7 +13,6 @@
 // result is the one loglik_many gives.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <mutex>
 
 #include "mvgeo.h"
@@ -95,7 +94,7 @@ int loglik_many_noalloc(const mvg_task *h_tasks, int n_tasks, double *h_loglik, 
               MVG_NOALLOC_SCRATCH_BYTES / 1e6);
     return MVG_ERR_LIMIT;
   }
-  const int slots = (int)(((size_t)MVG_NOALLOC_SCRATCH_BYTES - fixed) / slot);
+  small_layout(g_tasks, n_tasks, ((size_t)MVG_NOALLOC_SCRATCH_BYTES - fixed) / sizeof(double));
   char *base = nullptr;
   if (int rc = scratch_address(&base)) return rc;
   SmallTask *d_tasks = (SmallTask *)base;
@@ -107,8 +106,7 @@ int loglik_many_noalloc(const mvg_task *h_tasks, int n_tasks, double *h_loglik, 
     set_error("loglik_many_noalloc: task upload failed: %s", hipGetErrorString(hipGetLastError()));
     return MVG_ERR_LAUNCH;
   }
-  int rc = launch_small_loglik(d_tasks, g_tasks, n_tasks, nmax, d_ws,
-                               std::min(slots, small_batch_slots(n_tasks)), d_out, st);
+  int rc = launch_small_loglik(d_tasks, g_tasks, n_tasks, d_ws, d_out, st);
   if (!rc && hipMemcpyAsync(g_out, d_out, sizeof(double) * 4 * (size_t)n_tasks,
                             hipMemcpyDeviceToHost, st) != hipSuccess) {
     set_error("loglik_many_noalloc: result copy failed: %s", hipGetErrorString(hipGetLastError()));

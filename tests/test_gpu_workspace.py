@@ -63,3 +63,24 @@ def test_factor_times_vector(lib, n, nb):
     want = (low @ eps[:, None])[:, 0]
     low.abs_()
     assert bool(torch.all((out[0] - want).abs() <= 1e-13 * (low @ eps.abs()[:, None])[:, 0]))
+
+
+# the server admits a request by mvg_footprint: what a batch of small likelihoods
+# holds may not be more than its tasks' footprints (at any tile size) together
+@pytest.mark.parametrize("sizes", [[20] * 1023 + [512], [512] + [1] * 1100, [32, 33, 64, 65, 128, 300] * 20,
+                                   [512] * 64])
+def test_batch_within_footprints(lib, sizes):
+    print("workspace of a batch, n = %d .. %d" % (min(sizes), max(sizes)), flush=True)
+    data = {}
+    for n in set(sizes):
+        x, y = synthetic.jittered_grid(n, 1)
+        data[n] = (_dev(x), _dev(y), _dev(synthetic.normal_eps(2 * n, 1)), (1.0, 1.0, 0.1, 0.7, 1.0, 0.5))
+    got = []
+    held = _held(lambda: got.append(lib.loglik_many([data[n] for n in sizes])))
+    assert 0 < held <= sum(lib.mvg_footprint(n, {"nb": 128}) for n in sizes)
+    # the same bits as one by one, wherever a task's workspace lies
+    for n in set(sizes):
+        alone = lib.loglik_many([data[n]])
+        at = [i for i, s in enumerate(sizes) if s == n]
+        for key in ("loglik", "logdet", "quad", "status"):
+            assert (got[0][key][at] == alone[key][0]).all(), (n, key)

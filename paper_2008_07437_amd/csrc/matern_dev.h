@@ -63,19 +63,47 @@ __device__ __forceinline__ double quad_sums(double x, const double *__restrict__
   return qlev_h(j);
 }
 
-// Normalised Matern M(x; nu_o) for the three orders, x > 0, by the closed
-// forms and (QUAD: some order needs it) the quadrature (sq: its table).
-template <bool QUAD>
-__device__ __forceinline__ void matern3(double x, const MaternArgs &P,
-                                        const double *__restrict__ sq, double M[3]) {
-  if (x > qlev_xmax(QLEV - 1)) {
-    M[0] = M[1] = M[2] = 0.0;
-    return;
+// The same for x below the polynomials' first octave, from the table in memory
+// (their kernels hold the polynomials in LDS instead): all lanes of a wave are at
+// the same node, of level 0, so a node's values come by scalar loads.  Sigma of
+// 6,400 locations all that close (a = 1e5 on the unit square): 3.3 ms with vector
+// loads, 1.9 so (a pair of nodes loaded ahead takes registers: 2.6); the
+// quadrature alone, without polynomials, 2.2.
+static_assert(qlev_cnt(0) % 2 == 1, "nodes 1 .. cnt - 1 in pairs");
+__device__ __forceinline__ void quad_sums_near(double x, const double *qt, double s[3]) {
+  typedef const __attribute__((address_space(4))) double cdouble;
+  cdouble *q = (cdouble *)qt;
+  double s0 = 0.5, s1 = 0.5, s2 = 0.5;
+  for (int k = 1; k < qlev_cnt(0); k += 2) {
+    double u[8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      u[2 * i] = q[i * QN + k];
+      u[2 * i + 1] = q[i * QN + k + 1];
+    }
+    const double e = exp(-x * u[0]);
+    s0 += e * u[2];
+    s1 += e * u[4];
+    s2 += e * u[6];
+    const double e2 = exp(-x * u[1]);
+    const double t0 = e2 * u[3];
+    const double t1 = e2 * u[5];
+    const double t2 = e2 * u[7];
+    s0 += t0;
+    s1 += t1;
+    s2 += t2;
+    if (t0 <= 1e-17 * s0 && t1 <= 1e-17 * s1 && t2 <= 1e-17 * s2) break;
   }
-  const double ex = exp(-x);
-  double s[3] = {0.5, 0.5, 0.5}, logh = 0.0;
-  if (QUAD) logh = log(quad_sums(x, sq, s));
-  const double lx = log(x);
+  s[0] = s0;
+  s[1] = s1;
+  s[2] = s2;
+}
+
+// Normalised Matern M(x; nu_o) of the three orders from the closed forms or the
+// quadrature's sums s (times the step, of logarithm logh).
+__device__ __forceinline__ void matern3_orders(double x, const MaternArgs &P, const double s[3],
+                                               double logh, double M[3]) {
+  const double ex = exp(-x), lx = log(x);
 #pragma unroll
   for (int o = 0; o < 3; ++o) {
     switch (P.closed[o]) {
@@ -85,6 +113,20 @@ __device__ __forceinline__ void matern3(double x, const MaternArgs &P,
       default: M[o] = exp(P.nu[o] * lx - x + P.lnorm[o] + logh) * s[o]; break;
     }
   }
+}
+
+// The same for x > 0, by the closed forms and (QUAD: some order needs it) the
+// quadrature (sq: its table).
+template <bool QUAD>
+__device__ __forceinline__ void matern3(double x, const MaternArgs &P,
+                                        const double *__restrict__ sq, double M[3]) {
+  if (x > qlev_xmax(QLEV - 1)) {
+    M[0] = M[1] = M[2] = 0.0;
+    return;
+  }
+  double s[3] = {0.5, 0.5, 0.5}, logh = 0.0;
+  if (QUAD) logh = log(quad_sums(x, sq, s));
+  matern3_orders(x, P, s, logh, M);
 }
 
 // T_k(z) as powers of z: p[k][j]
@@ -164,7 +206,14 @@ __device__ __forceinline__ void matern3_tab(double x, const MaternArgs &P,
   const int row = (hi >> 18) - ((1023 + CT_LO) << 2);  // octave and its quarter
   static_assert(CT_SUB == 4, "the two leading mantissa bits name the part");
   if ((unsigned)row >= (unsigned)((CT_HI - CT_LO) * CT_SUB)) {
-    matern3<true>(x, P, qt, M);
+    if (x > qlev_xmax(QLEV - 1)) {
+      M[0] = M[1] = M[2] = 0.0;
+      return;
+    }
+    double s[3], h = qlev_h(0);
+    if (row < 0) quad_sums_near(x, qt, s);
+    else h = quad_sums(x, qt, s);
+    matern3_orders(x, P, s, log(h), M);
     return;
   }
   const double m = __hiloint2double((hi & 0xFFFFF) | 0x3FF00000, __double2loint(x));  // [1, 2)

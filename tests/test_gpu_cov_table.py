@@ -31,3 +31,23 @@ def test_table_edges(orc, nu, a):
     big = np.abs(ref) > 1e-280
     assert np.max(np.abs(got[big] - ref[big]) / np.abs(ref[big])) <= 2e-13
     assert np.all(np.abs(got[~big]) <= 1e-280)
+
+
+# distances below the first octave, where a pair falls back to the quadrature
+@pytest.mark.parametrize("nu", [(0.5, 1.0), (0.3, 0.9), (1.5, 0.7), (2.5, 4.9), (0.02, 5.0)])
+def test_below_the_table(orc, nu):
+    import torch
+    import paper_2008_07437_amd as mvg
+    th = (1.3, 0.8, 2.5, nu[0], nu[1], 0.4)
+    print("below the table nu=%s" % (nu,), flush=True)
+    first = 2.0 ** -14
+    x = np.concatenate([np.geomspace(1e-13, first, 400), [np.nextafter(first, 0), np.nextafter(first, 1)]])
+    xs = np.concatenate([[0.0], np.unique(x * th[2])])
+    d = torch.as_tensor(xs).cuda()
+    A = mvg.cov_generate(d, torch.zeros_like(d), th, {"nb": 256})
+    k = np.arange(1, xs.size)
+    r = np.concatenate([2 * k, 2 * k + 1, 2 * k + 1, 2 * k])
+    c = np.concatenate([0 * k, 0 * k + 1, 0 * k, 0 * k + 1])
+    got = A.gather(r, c).cpu().numpy()
+    ref = orc.cov_entries(xs, np.zeros_like(xs), th, r, c)
+    assert np.max(np.abs(got - ref) / np.abs(ref)) <= 2e-13

@@ -1385,8 +1385,14 @@ static void launch_panel(const QrTask *d_tasks, int ntask, int mmax, int p0, hip
 
 // Apply / sample workgroup size: 512 threads (8 waves share a column
 // block's rows), or 256 by MVG_QR_APPLY_THREADS=256 (experiments).  There is
-// no 1024-thread form: at 128 registers per lane it spills, and a run of it
-// took a GPU memory fault whose cause was not found.
+// no 1024-thread form, and none is to be run: at 128 registers per lane it
+// spills, and two runs of it ended in a GPU memory fault whose cause was not
+// found.  It is not an index of these kernels: formed on the host for every lane
+// at 256, 512 and 1024 threads (matrices of 32 to 1,536 rows, their panels and
+// column blocks), each lies in its buffer, 16-byte loads are aligned, and no
+// index but the waves' own LDS rows depends on the workgroup's size.  That does
+// not cover what the compiler makes of a kernel that spills; at 256 and 512
+// threads no vector register is spilled.
 static int apply_threads() {
   static const int t = [] {
     const char *e = getenv("MVG_QR_APPLY_THREADS");

@@ -472,7 +472,8 @@ void mvg_server_destroy(mvg_server *S);
  * and starts recording, mvg_prof_enable(0) stops.  mvg_prof_read sums the
  * records of one kind: MVG_PROF_TRAILING (the trailing-update GEMM kernel,
  * the FLOP sink of the factorisation; in the TLR factorisation its update
- * GEMM), MVG_PROF_SYRK (the look-ahead SYRK of the next diagonal tile), MVG_PROF_GEN (covariance
+ * GEMM; matrices of up to 8,192 rows and the last 8,192 rows of larger ones are
+ * factored in 64-wide steps, which are counted in MVG_PROF_POTRF alone), MVG_PROF_SYRK (the look-ahead SYRK of the next diagonal tile), MVG_PROF_GEN (covariance
  * generation), MVG_PROF_POTRF (whole factorisation), MVG_PROF_SOLVE (solve and
  * reductions), MVG_PROF_COKRIGE, MVG_PROF_LOWP (the FP32/BF16 off-band
  * update of the mixed-precision factorisation), MVG_PROF_IR (iterative

@@ -283,9 +283,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 // ------------------------------------------------------- look-ahead kernel
 //
-// Small (32 KB LDS, about 100 VGPRs per lane), so that it can be resident on
-// a CU next to two trailing-update workgroups: the look-ahead never waits for
-// the trailing GEMM to drain.
+// Small (32 KB LDS, about 100 VGPRs per lane), so that the next diagonal tile's
+// update (k_syrk64) can be resident on a CU next to two trailing-update
+// workgroups of 64 KB and does not wait for one to end.  The 64-wide steps that
+// factor the tile after it hold 76 KB: each of those waits until a trailing
+// block retires (up to 0.2 ms at nb = 1024).
 constexpr int PB = 64;
 constexpr int SMALL_LDS = 2 * 2 * PB * KB;  // doubles (32 KB)
 

@@ -1,5 +1,5 @@
-"""GPU checks of the batched small-problem likelihood (one persistent launch,
-one workgroup per task) against the FP64 oracle, and of its independence of
+"""GPU checks of the batched small-problem likelihood (all tasks together, one
+launch per 64 columns) against the FP64 oracle, and of its independence of
 the batch it runs in."""
 import sys
 

@@ -1031,12 +1031,15 @@ static int run_small(std::vector<SmallTask> &tasks, int64_t nmax, double *h_logl
   // where memory is short.
   const size_t least = small_workspace_doubles(nmax);
   size_t need = small_layout(tasks.data(), nt, SIZE_MAX);
-  size_t bytes = fixed + sizeof(double) * need, step = 4096, admitted = 0;
+  size_t bytes = fixed + sizeof(double) * need, step = 4096, admitted = 0, one = 0;
   while (step < bytes && step < ((size_t)1 << 30)) step *= 2;
   if (step < bytes) step = (size_t)1 << 27;
   mvg_opts o{};
   o.nb = 128;
-  for (const SmallTask &t : tasks) admitted += mvg_footprint(t.n, &o);
+  for (int i = 0; i < nt; ++i) {
+    if (i == 0 || tasks[i].n != tasks[i - 1].n) one = mvg_footprint(tasks[i].n, &o);
+    admitted += one;
+  }
   bytes = std::max(bytes, std::min((bytes + step - 1) / step * step, admitted));
   char *buf = nullptr;
   while (malloc_async((void **)&buf, bytes, st) != hipSuccess) {

@@ -23,9 +23,9 @@
 //
 // Bound by the FP64 matrix units and, with few tasks, by the chain of steps.
 // Measured against one workgroup per task in a persistent launch: 1024 theta
-// at n = 400 12.7 -> 9.6 ms (4.0 of it generation; steps at 50 % MFMA busy, 8
-// GB read), 192 tasks of n = 20..512 7.3 -> 2.0 ms (the largest task's latency
-// on its one workgroup had set it).
+// at n = 400 12.7 -> 7.5 ms (1.3 of it generation, 6.0 the steps, with the matrix
+// units 51 % busy, 17 GB read and 4 written), 192 tasks of n = 20..512 7.3 -> 1.8
+// ms (the largest task's latency on its one workgroup had set it).
 #include <algorithm>
 #include <cmath>
 

@@ -29,14 +29,14 @@
 // it reads was finished by the launch before, so there is nothing to wait for
 // inside a launch.
 //
-// Measured: 18 us a step while the chain bounds it (about 4 us of launch, 1.3
-// of loads, 10 of the 64 x 64 factor, the rest the products before it), 29 us
-// at 4,096 trailing rows and 62 at 6,400 (33 and 73 with one panel at a time
-// and 8-byte loads), where the rank-64 updates do: 36 us of matrix-core time
-// at 6,400, the rest waiting for operands at the blocks' starts and ends.  Before, a
-// step was three launches (factor 37 us, panel 5, update 9) and the inverse of
-// a tile 7 (nb = 512) or 15 more of 12 to 40 us each: 2n = 3,074 took 6.2 ms,
-// now 1.7; a 1024 tile 2 ms, now 0.3.
+// Measured: 21 us a step while the chain bounds it, up to 2,000 trailing rows
+// (about 4 us of launch, 1.3 of loads, 10 of the 64 x 64 factor, the rest the
+// products before it), 29 us at 3,100, 38 at 4,000 and 60 at 6,000, where the
+// rank-256 updates do: the matrix cores are busy half of that time, the rest is
+// waiting for operands at the blocks' starts and ends.  Before, a step was
+// three launches (factor 37 us, panel 5, update 9) and the inverse of a tile 7
+// (nb = 512) or 15 more of 12 to 40 us each: 2n = 3,074 took 6.2 ms, now 1.3; a
+// 1024 tile 2 ms, now 0.3.
 #include <algorithm>
 #include <cmath>
 

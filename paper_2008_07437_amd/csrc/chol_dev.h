@@ -451,8 +451,7 @@ __device__ __forceinline__ void row_step(const RowStep &a, double *sm, int64_t g
 // The operands go from memory to registers directly (the two waves that share
 // a half meet in the CU's cache), half a panel ahead of the products.  Row l
 // of MFMA tile t is row 2 l + t of the half, so that a load brings both tiles'
-// operands: with one tile's a load, the cache's lookups bound the update (17 a
-// load, 73 % of its cycles at 6,400 rows).
+// operands: with one tile's a load, the cache's lookups bound the update.
 template <class F>
 __device__ __forceinline__ void block_sub_nt(double *C, int n, F panel, int64_t ld, bool lower) {
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -788,7 +788,7 @@ static int panel_trsm(const TileMap &M, int k, const double *winv, double *P, hi
 // Trailing matrices of at most this many rows are factored in 64-wide steps
 // throughout (chol.hip): one launch of 20-100 us per step against a tile
 // step's chain of look-ahead, panel copy, panel solve and update.  Where the
-// 64-wide steps' updates, at 60 % of the matrix cores' rate, outweigh that:
+// 64-wide steps' updates, at 55 % of the matrix cores' rate, outweigh that:
 // whole evaluation of 7,500 rows, tiles from 6,144 5.1 ms, 64-wide throughout
 // 4.9; of 12,800, from 6,144 16.4 ms, from 8,192 and 9,216 16.15, from 10,240
 // 16.3.
